@@ -40,6 +40,8 @@ struct cd_plan {
     double *q;                    // [max_batch] per-token thresholds of the last per-token call
     float *lat;                   // [max_batch][d_rank] predictor latent
     float *part;                  // per-range partial sums of y (CD_PLAN_DETERMINISTIC)
+    void *cal;                    // calibration workspace (cal_bytes), grown by countdown_calibrate
+    size_t cal_bytes;
     unsigned phases;              // kernels launched per call (CD_PHASE_*)
     bool has_state;               // act / s hold a coefficient kernel's output
     bool s_in_coef;               // the last call's s is coef (ideal D, per-token thresholds)
@@ -402,7 +404,7 @@ cd_status dalloc(T **ptr, size_t count)
 
 void release(cd_plan *p)
 {
-    void *bufs[] = {p->act, p->s, p->coef, p->lat, p->q, p->part};
+    void *bufs[] = {p->act, p->s, p->coef, p->lat, p->q, p->part, p->cal};
     for (void *b : bufs)
         if (b)
             (void)hipFree(b);
@@ -567,6 +569,53 @@ cd_status countdown_ffn_dense(cd_plan *plan, const uint16_t *x, int B, const uin
 
 namespace {
 
+// Calibration workspace: [T] quantiles (fp64), the predictor's latents, the
+// coefficients of one chunk of tokens. It stays with the plan (up to
+// kCalibKeepBytes; a larger one is freed when the call ends), so that a second
+// calibration pays no allocation.
+constexpr int kCalibTokens = 256;
+constexpr size_t kCalibCoefBytes = 64u << 20;
+constexpr size_t kCalibKeepBytes = 128u << 20;
+
+struct CalibLayout {
+    size_t scratch, coef, bytes;  // byte offsets (the quantiles come first) and the total
+};
+
+CalibLayout calib_layout(const cd_plan *p, int variant, int tc, int T)
+{
+    const auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    CalibLayout l;
+    l.scratch = up((size_t)T * sizeof(double));
+    const size_t y = T <= p->max_batch ? (size_t)T * p->d_model : 0;  // the decode kernels' y
+    const size_t f = cdk::calib_scratch_floats(variant, tc, p->d_model, p->d_rank);
+    l.coef = l.scratch + up((f > y ? f : y) * sizeof(float));
+    l.bytes = l.coef + (size_t)tc * p->d_ff * sizeof(float);
+    return l;
+}
+
+void calib_free(cd_plan *p)
+{
+    if (p->cal)
+        (void)hipFree(p->cal);
+    p->cal = nullptr;
+    p->cal_bytes = 0;
+}
+
+// At least `bytes` of workspace (calls synchronise before they return, so nothing uses the old one).
+cd_status calib_reserve(cd_plan *p, size_t bytes)
+{
+    if (bytes <= p->cal_bytes)
+        return CD_OK;
+    calib_free(p);
+    char *b = nullptr;
+    const cd_status st = dalloc(&b, bytes);
+    if (st == CD_OK) {
+        p->cal = b;
+        p->cal_bytes = bytes;
+    }
+    return st;
+}
+
 cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uint16_t *W_gate,
                     const uint16_t *W_up, const uint16_t *A_t, const uint16_t *B_t,
                     const uint32_t *Tp, double k, float *thld_out, double *q_out, void *stream)
@@ -596,44 +645,70 @@ cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uin
     if (st != CD_OK)
         return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const int tb = p->max_batch;
-    float *coef = nullptr, *ybuf = nullptr;
-    double *q = nullptr;
-    st = dalloc(&coef, (size_t)tb * p->d_ff);
-    if (st == CD_OK) st = dalloc(&ybuf, (size_t)tb * p->d_model);
-    if (st == CD_OK) st = dalloc(&q, (size_t)T);
-    // The coefficient kernels run with thld = +inf (no neuron active) and
-    // write the dense coefficient vectors of up to max_batch tokens at a time.
-    const uint16_t *wg = W_gate ? W_gate : W_up;
-    const uint16_t *wu = W_up ? W_up : W_gate;  // CATS calibration reads W_gate only
-    for (int t0 = 0; st == CD_OK && t0 < T; t0 += tb) {
-        const int nb = T - t0 < tb ? T - t0 : tb;
-        const uint16_t *xb = X + (size_t)t0 * p->d_model;
-        if (pred) {
-            st = launched(cdk::launch_latent(xb, nb, A_t, p->d_model, p->d_rank, p->lat, s));
-            if (st != CD_OK)
-                break;
-        }
-        cdk::CoefArgs a = coef_args(p, xb, nb, wg, wu, B_t, INFINITY, ybuf, Tp);
-        a.coef = coef;
-        st = launched(cdk::launch_coef(variant, a, s));
-        if (st != CD_OK)
+    // Tokens go through in chunks whose coefficients stay within kCalibCoefBytes;
+    // smaller chunks when that does not fit in memory.
+    CalibLayout l;
+    const size_t fit = kCalibCoefBytes / ((size_t)p->d_ff * sizeof(float));
+    int tc = T < kCalibTokens ? T : kCalibTokens;
+    if (fit < (size_t)tc)
+        tc = fit > (size_t)p->max_batch ? (int)fit : p->max_batch;
+    for (;; tc /= 2) {
+        l = calib_layout(p, variant, tc, T);
+        st = calib_reserve(p, l.bytes);
+        if (st != CD_ENOMEM || tc == 1 || T <= p->max_batch)
             break;
-        st = launched(cdk::launch_select(coef, p->d_ff, p->d_ff, nb, pred || tern ? 0 : 1, k,
-                                         q + t0, s));
     }
-    // the act / s workspace now describes a calibration batch, not an FFN call
+    if (st != CD_OK)
+        return st;
+    char *ws = static_cast<char *>(p->cal);
+    double *q = reinterpret_cast<double *>(ws);
+    cdk::CalibArgs a;
+    a.d_model = p->d_model;
+    a.d_ff = p->d_ff;
+    a.d_rank = p->d_rank;
+    a.Wg = W_gate;
+    a.Wu = W_up;
+    a.At = A_t;
+    a.Bt = B_t;
+    a.Tp = Tp;
+    a.scratch = reinterpret_cast<float *>(ws + l.scratch);
+    a.coef = reinterpret_cast<float *>(ws + l.coef);
+    if (T <= p->max_batch) {
+        // one decode-sized batch: the FFN's own coefficient kernel reads the weights
+        // once too, and is 5-20 us faster than a matrix-product tile of 32 tokens
+        // (1 token of a 4096 x 11008 layer: 38 against 58 us a call)
+        if (pred)
+            st = launched(cdk::launch_latent(X, T, A_t, p->d_model, p->d_rank, p->lat, s));
+        cdk::CoefArgs c = coef_args(p, X, T, W_gate ? W_gate : W_up, W_up ? W_up : W_gate, B_t,
+                                    INFINITY, a.scratch, Tp);  // y: zeroed, not read
+        c.coef = a.coef;
+        if (st == CD_OK)
+            st = launched(cdk::launch_coef(variant, c, s));
+        if (st == CD_OK)
+            st = launched(cdk::launch_select(a.coef, p->d_ff, p->d_ff, T, pred || tern ? 0 : 1, k,
+                                             q, s));
+    } else {
+        for (int t0 = 0; st == CD_OK && t0 < T; t0 += tc) {
+            a.T = T - t0 < tc ? T - t0 : tc;
+            a.X = X + (size_t)t0 * p->d_model;
+            st = launched(cdk::launch_calib_coef(variant, a, s));
+            if (st == CD_OK)
+                st = launched(cdk::launch_select(a.coef, p->d_ff, p->d_ff, a.T, pred || tern ? 0 : 1,
+                                                 k, q + t0, s));
+        }
+    }
+    // a calibration is not an FFN call: down-only calls and exports need one first
     forget_state(p);
+    const bool q8 = (reinterpret_cast<uintptr_t>(q_out) & 7u) == 0;
     if (st == CD_OK)
-        st = hip_status(cdk::launch_mean(q, T, thld_out, s));
-    if (st == CD_OK && q_out)
+        st = hip_status(cdk::launch_mean(q, T, thld_out, q8 ? q_out : nullptr, s));
+    if (st == CD_OK && q_out && !q8)
         st = hip_status(hipMemcpyAsync(q_out, q, sizeof(double) * T, hipMemcpyDeviceToDevice, s));
     const hipError_t se = hipStreamSynchronize(s);
     if (st == CD_OK && se != hipSuccess)
         st = CD_EHIP;
-    if (coef) (void)hipFree(coef);
-    if (ybuf) (void)hipFree(ybuf);
-    if (q) (void)hipFree(q);
+    if (p->cal_bytes > kCalibKeepBytes)
+        calib_free(p);
     return st;
 }
 

@@ -104,4 +104,42 @@ __device__ __forceinline__ int lanes_below(uint64_t m)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Lanes whose chunk lies past the end of a row (ragged d_model) or of the
+// token batch load these 16 zero bytes instead: an address select before the
+// load rather than a select of the loaded data, which would make the compiler
+// wait for each load on its own.
+inline __device__ __align__(16) uint32_t kZeroChunk[4] = {0u, 0u, 0u, 0u};  // never written
+
+template <class T>
+__device__ __forceinline__ const T *or_zero(bool ok, const T *p)
+{
+    return ok ? p : reinterpret_cast<const T *>(kZeroChunk);
+}
+
+// ---- matrix cores: one 16 x 16 tile, 32 columns of the contraction per step
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kTile = 16;
+
+__device__ __forceinline__ f32x4_t mfma16(const u32x4 &a, const u32x4 &b, f32x4_t c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
+                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+// ---- packed ternary weights (layout: countdown.h, countdown_ternary_pack)
+
+constexpr uint32_t kTernLut = 0x00BF3F00u;  // bytes: code 0 -> 0x00, 1 -> 0x3F, 2 -> 0xBF
+constexpr uint32_t kTernPairMask = 0x03000300u;
+
+// bf16 pair (weights 2m, 2m + 1 of unit j's half of word W), each 0 or +-0.5
+// (in the FFN kernels j and m are compile-time constants after unrolling)
+__device__ __forceinline__ uint32_t tern_pair(uint32_t W, int j, int m)
+{
+    const uint32_t sel = (j & 1) ? (W << (8 - 2 * m)) & kTernPairMask : (W >> (2 * m)) & kTernPairMask;
+    return __builtin_amdgcn_perm(0u, kTernLut, sel);
+}
+
 } // namespace cdk

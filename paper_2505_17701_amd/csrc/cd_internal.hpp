@@ -90,7 +90,23 @@ constexpr int kTopkMaxDff = 32768;
 // Per-token linear-interpolation quantile of coef rows [T][ld] (n used entries).
 hipError_t launch_select(const float *coef, int ld, int n, int T, int use_abs, double k,
                          double *q_out, hipStream_t s);
-hipError_t launch_mean(const double *q, int T, float *out, hipStream_t s);
+// *out = mean of q[0, T) in fp64 (summed in order); q_out (may be NULL) gets a copy of q
+hipError_t launch_mean(const double *q, int T, float *out, double *q_out, hipStream_t s);
+// Dense coefficients of T tokens at once: coef [T][d_ff] of the variant (u for M,
+// SiLU(g) for CATS, s for ideal D, s_hat for the predictors). scratch:
+// calib_scratch_floats floats.
+struct CalibArgs {
+    const uint16_t *X;   // [T][d_model] bf16
+    int T, d_model, d_ff, d_rank;
+    const uint16_t *Wg, *Wu;  // [d_ff][d_model], those the variant reads
+    const uint16_t *At;  // [d_rank][d_model]
+    const uint16_t *Bt;  // [d_ff][d_rank]
+    const uint32_t *Tp;  // packed ternary predictor
+    float *scratch;
+    float *coef;
+};
+size_t calib_scratch_floats(int variant, int T, int d_model, int d_rank);
+hipError_t launch_calib_coef(int variant, const CalibArgs &a, hipStream_t s);
 // Measurement aid: plain streaming read of bytes (a multiple of 16) at src.
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, hipStream_t s);
 

@@ -44,18 +44,6 @@ __device__ __forceinline__ u32x4 load16_stream(const uint16_t *p)
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
 
-// Lanes whose chunk lies past the end of a row (ragged d_model) or of the
-// token batch load these 16 zero bytes instead: an address select before the
-// load rather than a select of the loaded data, which would make the compiler
-// wait for each load on its own.
-__device__ __align__(16) uint32_t kZeroChunk[4] = {0u, 0u, 0u, 0u};  // never written
-
-template <class T>
-__device__ __forceinline__ const T *or_zero(bool ok, const T *p)
-{
-    return ok ? p : reinterpret_cast<const T *>(kZeroChunk);
-}
-
 template <int NK>
 __device__ __forceinline__ void load_row(u32x4 (&w)[NK], const uint16_t *__restrict__ row,
                                          int d_model, int lane)
@@ -639,17 +627,6 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_pred(const CoefArgs a)
 // column order. The four waves take a quarter of the steps each and add
 // their 16 x 16 partial sums in LDS; lane l holds D[4 (l / 16) + r][l % 16].
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kTile = 16;
-
-__device__ __forceinline__ f32x4_t mfma16(const u32x4 &a, const u32x4 &b, f32x4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-
 // LDS token rows for the MFMA kernel: a 16-byte pad per row keeps the 16
 // tokens of one step on distinct banks; one zero chunk serves tokens >= B.
 template <int NK>
@@ -964,9 +941,6 @@ struct TernShape {
     static constexpr int kWords = NK >= 2 ? NK / 2 : 1;  // per lane and row
 };
 
-constexpr uint32_t kTernLut = 0x00BF3F00u;  // bytes: code 0 -> 0x00, 1 -> 0x3F, 2 -> 0xBF
-constexpr uint32_t kTernPairMask = 0x03000300u;
-
 template <int NK>
 struct TernRows {
     static constexpr int kW = TernShape<NK>::kWords;
@@ -1000,14 +974,6 @@ struct TernRows {
         }
     }
 };
-
-// bf16 pair (weights 2m, 2m + 1 of unit j's half of word W), each 0 or +-0.5
-// (j and m are compile-time constants after unrolling)
-__device__ __forceinline__ uint32_t tern_pair(uint32_t W, int j, int m)
-{
-    const uint32_t sel = (j & 1) ? (W << (8 - 2 * m)) & kTernPairMask : (W >> (2 * m)) & kTernPairMask;
-    return __builtin_amdgcn_perm(0u, kTernLut, sel);
-}
 
 // s_hat_b = x_b . theta[:, row] for the wave's rows (xget(b, j) = this lane's
 // 16-byte chunk j of token b), the signed threshold with the union over the
@@ -1949,14 +1915,32 @@ __global__ __launch_bounds__(kSelThreads) void k_select_quantile(const float *__
         q[blockIdx.x] = v0 + (h - (double)lo) * (v1 - v0);
 }
 
-__global__ void k_mean(const double *__restrict__ q, int T, float *__restrict__ out)
+// The mean of q[0, T) in fp64, added in order by one thread from LDS (a chain of
+// dependent global loads took 11.8 us at 256 tokens); the others fetch the next
+// values and copy them to q_out.
+__global__ __launch_bounds__(kBlock) void k_mean(const double *__restrict__ q, int T,
+                                                 float *__restrict__ out,
+                                                 double *__restrict__ q_out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int t = 0; t < T; ++t)
-            s += q[t];
-        *out = (float)(s / (double)T);
+    __shared__ double v[kBlock];
+    double s = 0.0;
+    for (int t0 = 0; t0 < T; t0 += kBlock) {
+        const int i = t0 + threadIdx.x;
+        const double mine = i < T ? q[i] : 0.0;
+        __syncthreads();
+        v[threadIdx.x] = mine;
+        if (q_out && i < T)
+            q_out[i] = mine;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int n = min(T - t0, kBlock);
+#pragma unroll 16
+            for (int t = 0; t < n; ++t)
+                s += v[t];
+        }
     }
+    if (threadIdx.x == 0)
+        *out = (float)(s / (double)T);
 }
 
 // ------------------------------------------------- per-token threshold path
@@ -3222,10 +3206,12 @@ hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, hip
     return hipGetLastError();
 }
 
-hipError_t launch_mean(const double *q, int T, float *out, hipStream_t s)
+hipError_t launch_mean(const double *q, int T, float *out, double *q_out, hipStream_t s)
 {
-    k_mean<<<1, 64, 0, s>>>(q, T, out);
+    k_mean<<<1, kBlock, 0, s>>>(q, T, out, q_out);
     return hipGetLastError();
 }
 
 } // namespace cdk
+
+#include "cd_calib.hpp"
