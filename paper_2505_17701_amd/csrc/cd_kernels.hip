@@ -8,16 +8,16 @@
 //     against x (registers for one token, and for two of d_model <= 4096 in
 //     the two-row kernel; otherwise an LDS copy per workgroup) with
 //     v_dot2_f32_bf16, reduces across the wave with DPP and applies the
-//     strict threshold (union over the batch). For M-CountDown an active
+//     strict threshold (union over the batch). Batches of 3-8 run the MFMA
+//     kernels of cd_batch.hpp instead. For M-CountDown an active
 //     neuron's wave immediately reads its W_gate row and forms s = u *
 //     SiLU(g). Results land in per-neuron arrays act[d_ff] and s[B][d_ff];
 //     there are no barriers between waves. The kernel also zeroes y.
 //   predictor (practical D-CountDown): the latent x . theta_A (one workgroup
 //     per A_t row), then a coefficient kernel over blocks of 32 neurons: B_t
 //     scores, signed threshold, and the block's active neurons dealt to its
-//     waves for the W_gate / W_up gather (v_dot2 up to 4 tokens, MFMA tiles
-//     of 16 neurons with the rows staged through LDS for 5-8). The ternary
-//     predictor scores from its 2-bit packed theta instead, with no latent.
+//     waves for the W_gate / W_up gather. The ternary predictor scores from
+//     its 2-bit packed theta instead, with no latent.
 //   down kernel: workgroup (c, g) owns a column chunk c and a contiguous
 //     neuron range g. One round trip reads act and s of the range, a wave
 //     ballot compacts the active neurons in ascending order into LDS; for 1-2
@@ -344,30 +344,30 @@ struct LatentStage {
     }
 };
 
-// Shape of one wave's B_t work at rank d_rank = 8 << LCPR: its kPredRowsPerWave
-// rows are one flat run of 16-byte chunks, chunk f on lane f % 64, kLoads per
+// Shape of one wave's B_t work at rank d_rank = 8 << LCPR: its R rows are one
+// flat run of 16-byte chunks, chunk f on lane f % 64, kLoads per
 // lane. A row is a segment of min(cpr, 64) lanes (summed by DPP) spread over
 // kJpr consecutive loads when it is longer than 64 chunks.
-template <int LCPR>
+template <int LCPR, int R = kPredRowsPerWave>
 struct PredShape {
     static constexpr int kCpr = 1 << LCPR;  // 16-byte chunks per B_t row
-    static constexpr int kLoads = kCpr * kPredRowsPerWave >= kWave ? kCpr * kPredRowsPerWave / kWave : 1;
+    static constexpr int kLoads = kCpr * R >= kWave ? kCpr * R / kWave : 1;
     static constexpr int kJpr = kCpr > kWave ? kCpr / kWave : 1;
     static constexpr int kSegLog = LCPR < 6 ? LCPR : 6;
     static constexpr int kSeg = 1 << kSegLog;
 };
 
-template <int LCPR>
-__device__ __forceinline__ void pred_issue_bt(u32x4 (&wb)[PredShape<LCPR>::kLoads],
+template <int LCPR, int R = kPredRowsPerWave>
+__device__ __forceinline__ void pred_issue_bt(u32x4 (&wb)[(PredShape<LCPR, R>::kLoads)],
                                               const CoefArgs &a, int wr0, int lane)
 {
-    using S = PredShape<LCPR>;
+    using S = PredShape<LCPR, R>;
 #pragma unroll
     for (int j = 0; j < S::kLoads; ++j) {
         const int f = j * kWave + lane;
         const int rw = f >> LCPR;
         wb[j] = zero16();
-        if (rw < kPredRowsPerWave && wr0 + rw < a.d_ff)
+        if (rw < R && wr0 + rw < a.d_ff)
             wb[j] = load16_stream(a.Bt + (size_t)(wr0 + rw) * a.d_rank + (f & (S::kCpr - 1)) * 8);
     }
 }
@@ -404,12 +404,12 @@ struct LatentRegs {
 // the LDS copy lat for rank 1024), the signed threshold with the union over
 // the batch, act[] and (optionally) the coefficients. Returns the
 // wave-uniform mask of its active rows.
-template <int B, int LCPR>
-__device__ __forceinline__ uint32_t pred_score(const u32x4 (&wb)[PredShape<LCPR>::kLoads],
+template <int B, int LCPR, int R = kPredRowsPerWave>
+__device__ __forceinline__ uint32_t pred_score(const u32x4 (&wb)[(PredShape<LCPR, R>::kLoads)],
                                                const LatentRegs<B, LCPR> &lr, const float *lat,
                                                const CoefArgs &a, int wr0, int lane)
 {
-    using S = PredShape<LCPR>;
+    using S = PredShape<LCPR, R>;
     const bool seg_end = (lane & (S::kSeg - 1)) == S::kSeg - 1;
     float acc[B];
     zero_acc(acc);
@@ -436,7 +436,7 @@ __device__ __forceinline__ uint32_t pred_score(const u32x4 (&wb)[PredShape<LCPR>
         // the segment ends of this load close its rows
         const int rw = f >> LCPR;
         const int row = wr0 + rw;
-        const bool live = seg_end && rw < kPredRowsPerWave && row < a.d_ff;
+        const bool live = seg_end && rw < R && row < a.d_ff;
         bool act = false;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
@@ -455,7 +455,7 @@ __device__ __forceinline__ uint32_t pred_score(const u32x4 (&wb)[PredShape<LCPR>
         for (int i = 0; i < kWave / S::kSeg; ++i) {
             const int end = (i + 1) * S::kSeg - 1;        // lane of segment i's sum
             const int rwi = (j * kWave + end) >> LCPR;    // its row within the wave
-            if (rwi < kPredRowsPerWave)
+            if (rwi < R)
                 wmask |= (uint32_t)((m >> end) & 1u) << rwi;
         }
     }
@@ -483,7 +483,7 @@ __device__ __forceinline__ void pred_finish(const CoefArgs &a, const Tokens<B, N
 
 // Next neuron of this wave's share of the block mask (every fourth active
 // neuron), or -1; advances the mask past it.
-template <int NW = kWavesPerBlock>
+template <int NW>
 __device__ __forceinline__ int pred_next(uint32_t &m)
 {
     if (!m)
@@ -498,7 +498,6 @@ __device__ __forceinline__ int pred_next(uint32_t &m)
 // This wave's share of the block's active neurons: the waves' masks are
 // joined (one barrier) and every fourth active neuron, starting at number
 // `wave`, is kept.
-template <int NW = kWavesPerBlock>
 __device__ __forceinline__ uint32_t block_share(uint32_t *wflag, uint32_t wmask, int wave, int lane)
 {
     if (lane == 0 && wave < kWavesPerBlock)  // the scoring waves
@@ -516,14 +515,12 @@ __device__ __forceinline__ uint32_t block_share(uint32_t *wflag, uint32_t wmask,
 // Gather of the wave's share m of the block's active neurons (block base r0):
 // W_gate and W_up rows, s = u * SiLU(g), the next neuron's rows in flight
 // while the current one is reduced.
-template <int B, int NK, bool XREG, int NW = kWavesPerBlock>
+template <int B, int NK, bool XREG, int NW>
 __device__ __forceinline__ void gather_rr(const CoefArgs &a, const Tokens<B, NK, XREG> &tok,
                                           uint32_t m, int r0, int lane)
 {
-    // the next neuron's W_gate + W_up rows in flight while the current one is
-    // reduced, for 1-2 tokens; at 4 the second buffer cost occupancy (168 against
-    // 100 VGPRs) and one buffer measured 1.5-4% faster (8B shape)
-    constexpr bool kPrefetch = NK <= 8 && B <= 2;
+    // the next neuron's W_gate + W_up rows in flight while the current one is reduced
+    constexpr bool kPrefetch = NK <= 8 && NW == kWavesPerBlock;
     int ra = pred_next<NW>(m);
     if (ra < 0)
         return;
@@ -564,8 +561,8 @@ __device__ __forceinline__ void gather_rr(const CoefArgs &a, const Tokens<B, NK,
 
 // Practical D-CountDown coefficient kernel (Sec. 4). A workgroup owns a block
 // of kPredRows neurons (kPredRowsPerWave per wave). One round of loads brings
-// the wave's B_t rows, the tokens (registers for batches of 1-2, this
-// thread's share of an LDS copy for 4-8) and the latent (staged in LDS).
+// the wave's B_t rows, the tokens (registers, or this thread's share of an LDS
+// copy) and the latent.
 // Each wave scores its rows (s_hat = latent . B_t[row], signed threshold,
 // union over the batch); the block's active neurons are then dealt
 // round-robin to the four waves, which gather their W_gate and W_up rows
@@ -614,308 +611,8 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_pred(const CoefArgs a)
         tok.write(xs);  // (block_share's barrier publishes the LDS copy)
     else
         tok.lds = xs;
-    uint32_t m = block_share<NWV>(wflag, wmask, wave, lane);
+    uint32_t m = block_share(wflag, wmask, wave, lane);
     gather_rr<B, NK, XREG, NWV>(a, tok, m, r0, lane);
-}
-
-// ------------------------------------------- MFMA gather for batches of 5-8
-// For 4-8 tokens the gathered products are small dense contractions: a tile
-// of 16 active neurons times the batch, on v_mfma_f32_16x16x32_bf16. Lane
-// l = i + 16 g (i = l % 16, g = l / 16) supplies row i of the tile (A operand)
-// and token i of the batch (B operand, zero for i >= B), each with the 8
-// columns 32 s + 8 g + [0, 8) of step s, so both operands use the same
-// column order. The four waves take a quarter of the steps each and add
-// their 16 x 16 partial sums in LDS; lane l holds D[4 (l / 16) + r][l % 16].
-
-// LDS token rows for the MFMA kernel: a 16-byte pad per row keeps the 16
-// tokens of one step on distinct banks; one zero chunk serves tokens >= B.
-template <int NK>
-struct MfmaTokLayout {
-    static constexpr int kCols = NK * kColsPerLoad;
-    static constexpr int kStride = kCols / 2 + 4;  // u32 per token row
-};
-
-template <int B, int NK>
-__host__ __device__ constexpr size_t mfma_lds_tokens_u32()
-{
-    return (size_t)B * MfmaTokLayout<NK>::kStride + 4;
-}
-
-// The tokens of the MFMA kernels: every thread's share of the LDS copy is
-// loaded with the kernel's first loads (issue) and written after (write);
-// the caller synchronises the workgroup before the copy is read.
-template <int B, int NK>
-struct MfmaTokens {
-    using TL = MfmaTokLayout<NK>;
-    static constexpr int kChunksPerTok = TL::kCols / 8;
-    static constexpr int kTotal = B * kChunksPerTok;
-    static constexpr int kIter = (kTotal + kBlock - 1) / kBlock;
-    u32x4 stage[kIter];
-
-    __device__ __forceinline__ void issue(const CoefArgs &a)
-    {
-#pragma unroll
-        for (int t = 0; t < kIter; ++t) {
-            const int c = threadIdx.x + t * kBlock;
-            const int b = c / kChunksPerTok, col = (c % kChunksPerTok) * 8;
-            stage[t] = load16(or_zero(c < kTotal && b < a.nb && col < a.d_model,
-                                      a.x + (size_t)b * a.d_model + col));
-        }
-    }
-
-    // the rows [B][kStride] and, after them, one zero chunk (returned)
-    __device__ __forceinline__ uint32_t *write(uint32_t *xs) const
-    {
-#pragma unroll
-        for (int t = 0; t < kIter; ++t) {
-            const int c = threadIdx.x + t * kBlock;
-            if (c < kTotal)
-                *reinterpret_cast<u32x4 *>(xs + (size_t)(c / kChunksPerTok) * TL::kStride +
-                                           (c % kChunksPerTok) * 4) = stage[t];
-        }
-        uint32_t *zchunk = xs + (size_t)B * TL::kStride;
-        if (threadIdx.x == 0)
-            *reinterpret_cast<u32x4 *>(zchunk) = zero16();
-        return zchunk;
-    }
-};
-
-// MFMA gather with the weight rows staged in LDS. Loads in the MFMA operand
-// layout (16 rows x 64 B per instruction) reach about 60% of the HBM rate of
-// row-contiguous loads on gathered rows (measured), so a wave loads each
-// batch of STEPS steps (32 columns each) of its tile's 16 W_gate and W_up rows
-// with 4 STEPS lanes on each row's piece (256 B of a row per load at 4 steps,
-// 512 B at 8), writes them to its own LDS tile (rows padded by 16 B) and
-// reads the A operands back; the token operand (L2-resident) is loaded with
-// the batch.
-template <int STEPS>
-struct WtShape {
-    static constexpr int kCols = STEPS * 32;              // columns of a batch
-    static constexpr int kStride = kCols + 8;             // bf16 per tile row
-    static constexpr int kWaveElems = 2 * kTile * kStride;  // bf16 per wave: W_gate and W_up tiles
-    static constexpr int kLanesPerRow = kCols / 8;        // lanes on one row's piece
-    static constexpr int kRowsPerLoad = kWave / kLanesPerRow;
-    static constexpr int kLoads = kTile / kRowsPerLoad;   // loads per lane and matrix
-};
-
-// batch widths: the low-rank kernel's 256 columns with one batch in flight
-// per wave measured 1-1.5% faster at 5-8 tokens than 128 columns with two in
-// flight (two 256-column batches take 254 VGPRs, one wave per SIMD); the
-// ternary kernel, and the low-rank one at rank 1024 (latent in LDS), keep
-// 128-column batches, two in flight (with 256 columns the ternary layer took
-// 80.7 against 64.4 us at 8 tokens)
-constexpr int kWtStepsWide = 8;
-constexpr int kWtStepsNarrow = 4;
-
-template <int STEPS>
-struct WtBatch {
-    using W = WtShape<STEPS>;
-    u32x4 w[2 * W::kLoads];  // W_gate rows kRowsPerLoad q + lane / kLanesPerRow, then W_up
-    u32x4 x[STEPS];
-};
-
-template <int STEPS>
-__device__ __forceinline__ void wt_load(WtBatch<STEPS> &bt, const CoefArgs &a,
-                                        const int (&row)[WtShape<STEPS>::kLoads], uint32_t have,
-                                        const uint16_t *xrow, bool xreal, int s, int s1, int lane)
-{
-    using W = WtShape<STEPS>;
-    const int g = lane / kTile;
-    const int col = s * 32 + (lane % W::kLanesPerRow) * 8;
-    const bool colok = col < s1 * 32 && col < a.d_model;
-#pragma unroll
-    for (int q = 0; q < W::kLoads; ++q) {
-        bt.w[q] = zero16();
-        bt.w[W::kLoads + q] = zero16();
-        if (((have >> q) & 1u) && colok) {
-            bt.w[q] = load16_stream(a.Wg + (size_t)row[q] * a.d_model + col);
-            bt.w[W::kLoads + q] = load16_stream(a.Wu + (size_t)row[q] * a.d_model + col);
-        }
-    }
-    // a batch inside the row needs no column checks; lanes past the batch read
-    // token 0 there (xrow), which only feeds output columns that are never
-    // stored (MFMA output column j depends on B column j alone)
-    if ((s + STEPS) * 32 <= a.d_model) {  // uniform
-#pragma unroll
-        for (int q = 0; q < STEPS; ++q)
-            bt.x[q] = load16(xrow + (s + q) * 32 + g * 8);
-    } else {
-#pragma unroll
-        for (int q = 0; q < STEPS; ++q) {
-            const int xc = (s + q) * 32 + g * 8;
-            bt.x[q] = load16(or_zero(xreal && xc < a.d_model, xrow + xc));
-        }
-    }
-}
-
-template <int STEPS>
-__device__ __forceinline__ void wt_consume(uint16_t *wt, const WtBatch<STEPS> &bt, int s, int s1,
-                                           int lane, f32x4_t &dg, f32x4_t &du)
-{
-    using W = WtShape<STEPS>;
-    const int i = lane % kTile, g = lane / kTile;
-    const int c = (lane % W::kLanesPerRow) * 8, rr0 = lane / W::kLanesPerRow;
-#pragma unroll
-    for (int q = 0; q < W::kLoads; ++q) {
-        const int rr = W::kRowsPerLoad * q + rr0;
-        *reinterpret_cast<u32x4 *>(wt + rr * W::kStride + c) = bt.w[q];
-        *reinterpret_cast<u32x4 *>(wt + (kTile + rr) * W::kStride + c) = bt.w[W::kLoads + q];
-    }
-#pragma unroll
-    for (int q = 0; q < STEPS; ++q) {
-        if (s + q < s1) {  // uniform
-            const u32x4 ga = *reinterpret_cast<const u32x4 *>(wt + i * W::kStride + q * 32 + g * 8);
-            const u32x4 ua =
-                *reinterpret_cast<const u32x4 *>(wt + (kTile + i) * W::kStride + q * 32 + g * 8);
-            dg = mfma16(ga, bt.x[q], dg);
-            du = mfma16(ua, bt.x[q], du);
-        }
-    }
-}
-
-// The block's active neurons (bits of M, rows r0 + bit) in tiles of 16 on MFMA:
-// each tile's column steps are split among 4 / ntiles waves, which add their
-// 16 x 16 partial sums in `part` (LDS [4][2][256] fp32) and write s = u * SiLU(g).
-// wtiles: LDS [4 waves][WtShape<STEPS>::kWaveElems] bf16; lrow: LDS [32] rows
-// of the active neurons. INTERLEAVE: wave kw of a tile takes batches kw,
-// kw + wpt, ... of STEPS steps, so the tile's waves read adjacent pieces of
-// each row together (after the low-rank score: 57.5 -> 56.7 us per 8B layer at
-// 8 tokens); otherwise each takes one contiguous run of steps (the ternary
-// kernel: interleaved, its layer took 68.2 against 65.4 us). A wave keeps two
-// batches in flight at 4 steps, one at 8.
-template <int B, int NK, bool INTERLEAVE, int STEPS>
-__device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wtiles, float *part,
-                                                int *lrow, uint32_t M, int r0, int wave, int lane)
-{
-    using W = WtShape<STEPS>;
-    constexpr int kWtSteps = STEPS, kWtLoads = W::kLoads;
-    const int n = __builtin_popcount(M);
-    if (threadIdx.x < kPredRows && ((M >> threadIdx.x) & 1u))
-        lrow[__builtin_popcount(M & ((1u << threadIdx.x) - 1u))] = r0 + threadIdx.x;
-    __syncthreads();  // lrow visible; the LDS scratch is free
-
-    const int ntiles = (n + kTile - 1) / kTile;  // 0, 1 or 2
-    if (ntiles == 0)
-        return;
-    const int wpt = kWavesPerBlock / ntiles;
-    const int t0 = (wave / wpt) * kTile, kw = wave % wpt;
-    const int i = lane % kTile, g = lane / kTile;
-    const int steps = (a.d_model + 31) / 32;
-    const int nbat = (steps + kWtSteps - 1) / kWtSteps;  // batches of kWtSteps steps
-    (void)nbat;
-    const bool xreal = i < a.nb;
-    const uint16_t *xrow = a.x + (size_t)(xreal ? i : 0) * a.d_model;
-    int row[kWtLoads];
-    uint32_t have = 0u;
-#pragma unroll
-    for (int q = 0; q < kWtLoads; ++q) {
-        const int k = t0 + W::kRowsPerLoad * q + lane / W::kLanesPerRow;
-        row[q] = k < n ? lrow[k] : r0;
-        have |= (k < n ? 1u : 0u) << q;
-    }
-    uint16_t *wt = wtiles + (size_t)wave * W::kWaveElems;
-    f32x4_t dg = {0.0f, 0.0f, 0.0f, 0.0f}, du = {0.0f, 0.0f, 0.0f, 0.0f};
-    WtBatch<STEPS> b0, b1;  // 4 steps: the next batch is in flight while this one is consumed
-    if constexpr (INTERLEAVE && STEPS >= kWtStepsWide) {
-        for (int j = kw; j < nbat; j += wpt) {
-            wt_load(b0, a, row, have, xrow, xreal, j * kWtSteps, steps, lane);
-            wt_consume(wt, b0, j * kWtSteps, steps, lane, dg, du);
-        }
-    } else if constexpr (INTERLEAVE) {
-        if (kw < nbat)
-            wt_load(b0, a, row, have, xrow, xreal, kw * kWtSteps, steps, lane);
-        for (int j = kw; j < nbat; j += 2 * wpt) {
-            const int jb = j + wpt;
-            if (jb < nbat)
-                wt_load(b1, a, row, have, xrow, xreal, jb * kWtSteps, steps, lane);
-            wt_consume(wt, b0, j * kWtSteps, steps, lane, dg, du);
-            if (jb >= nbat)
-                break;
-            if (jb + wpt < nbat)
-                wt_load(b0, a, row, have, xrow, xreal, (jb + wpt) * kWtSteps, steps, lane);
-            wt_consume(wt, b1, jb * kWtSteps, steps, lane, dg, du);
-        }
-    } else {
-        const int sw = (steps + wpt - 1) / wpt;  // this wave's steps [s0, s1)
-        const int s0 = min(steps, kw * sw), s1 = min(steps, s0 + sw);
-        wt_load(b0, a, row, have, xrow, xreal, s0, s1, lane);
-        for (int s = s0; s < s1; s += 2 * kWtSteps) {
-            const int sb = s + kWtSteps;
-            if (sb < s1)
-                wt_load(b1, a, row, have, xrow, xreal, sb, s1, lane);
-            wt_consume(wt, b0, s, s1, lane, dg, du);
-            if (sb >= s1)
-                break;
-            if (sb + kWtSteps < s1)
-                wt_load(b0, a, row, have, xrow, xreal, sb + kWtSteps, s1, lane);
-            wt_consume(wt, b1, sb, s1, lane, dg, du);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int e = (4 * g + r) * kTile + i;  // D[4g + r][i]
-        part[(wave * 2 + 0) * 256 + e] = dg[r];
-        part[(wave * 2 + 1) * 256 + e] = du[r];
-    }
-    __syncthreads();
-    const int ti = threadIdx.x / kTile, tj = threadIdx.x % kTile;  // D[ti][tj] of each tile
-    for (int tile = 0; tile < ntiles; ++tile) {
-        float gs = 0.0f, us = 0.0f;
-        for (int v = tile * wpt; v < (tile + 1) * wpt; ++v) {
-            gs += part[(v * 2 + 0) * 256 + threadIdx.x];
-            us += part[(v * 2 + 1) * 256 + threadIdx.x];
-        }
-        const int rank = tile * kTile + ti;
-        if (rank < n && tj < a.nb)
-            a.s[(size_t)tj * a.d_ff + lrow[rank]] = us * silu(gs);
-    }
-}
-
-// Practical D-CountDown coefficient kernel for batches of 4-8 (Sec. 4): the
-// scoring of k_coef_pred, then the block's active neurons in tiles of 16 on MFMA.
-template <int B, int NK, int LCPR>
-__global__ __launch_bounds__(kBlock) void k_coef_pred_mfma(const CoefArgs a)
-{
-    // LDS: the waves' weight tiles [4][kWaveElems] bf16, then the latent [B][d_rank]
-    // fp32 (rank 1024 only), whose space later holds the partial sums [4][2][16 x 16]
-    extern __shared__ __align__(16) uint32_t xs[];
-    __shared__ uint32_t wflag[kWavesPerBlock];
-    __shared__ int lrow[kPredRows];
-    using S = PredShape<LCPR>;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int r0 = blockIdx.x * kPredRows;
-    const int wr0 = r0 + wave * kPredRowsPerWave;
-
-    using LR = LatentRegs<B, LCPR>;
-    u32x4 wb[S::kLoads];
-    pred_issue_bt<LCPR>(wb, a, wr0, lane);
-    LR lr;
-    lr.issue(a.lat, a.nb, a.d_rank, lane);
-    LatentStage<LR::kRegs ? 1 : B> ls;  // the LDS copy, rank 1024 only
-    if constexpr (!LR::kRegs)
-        ls.issue(a.lat, a.nb, a.d_rank);
-    __builtin_amdgcn_sched_barrier(0);
-    zero_y(a.y, a.nb * a.d_model);
-    uint16_t *wtiles = reinterpret_cast<uint16_t *>(xs);
-    constexpr int STEPS = LR::kRegs ? kWtStepsWide : kWtStepsNarrow;
-    uint32_t *latw = xs + kWavesPerBlock * WtShape<STEPS>::kWaveElems / 2;
-    if constexpr (!LR::kRegs) {
-        ls.write(reinterpret_cast<u32x4 *>(latw), a.lat, a.nb, a.d_rank);
-        __syncthreads();
-    }
-
-    const uint32_t wmask = pred_score<B, LCPR>(wb, lr, reinterpret_cast<const float *>(latw), a,
-                                               wr0, lane);
-    if (lane == 0)
-        wflag[wave] = wmask;
-    __syncthreads();
-    uint32_t M = 0;
-#pragma unroll
-    for (int v = 0; v < kWavesPerBlock; ++v)
-        M |= wflag[v] << (v * kPredRowsPerWave);
-    // the latent is no longer read once gather_mfma_lds's first barrier has passed
-    gather_mfma_lds<B, NK, true, STEPS>(a, wtiles, reinterpret_cast<float *>(latw), lrow, M, r0,
-                                        wave, lane);
 }
 
 // ------------------------------------------------ ternary predictor
@@ -1042,80 +739,7 @@ __device__ __forceinline__ uint32_t tern_score(const TernRows<NK> &t, XF xget, c
     return wmask;
 }
 
-// The ternary score of a wave's kPredRowsPerWave rows on MFMA, for batches of
-// 5-8 and d_model 4096 (one 16-byte block of packed theta per lane and row):
-// s_hat = theta . x is a dense product with weights in {-1, 0, +1}. Lane
-// (n, g) = (lane % 16, lane / 16) reads block 4 t + g of row n (rows past the
-// wave's 8 read zeros) for t = 0 .. 15; unit j of that block, decoded by
-// tern_pair into 8 bf16 weights of +-0.5 or 0, is the A operand of one
-// v_mfma_f32_16x16x32_bf16 step whose B operand is token n's columns
-// 512 j + 8 (4 t + g) + [0, 8) from the LDS copy, so A and B agree on the
-// column order and the 128 steps cover every column once. D[row][token] is
-// half the score. Threshold, union and stores as in tern_score.
-template <int NK>
-struct TernMfmaRows {
-    static_assert(NK == 8, "one 16-byte block per lane and row");
-    static constexpr int kW = TernShape<NK>::kWords;  // 4
-    u32x4 blk[16];
-
-    __device__ __forceinline__ void issue(const CoefArgs &a, int wr0, int lane)
-    {
-        const int n = lane % kTile, g = lane / kTile;
-        const int row = wr0 + n;
-        const bool ok = n < kPredRowsPerWave && row < a.d_ff;
-        const uint32_t *rp = a.Tp + (size_t)(ok ? row : 0) * kWave * kW;
-#pragma unroll
-        for (int t = 0; t < 16; ++t)
-            blk[t] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4 *>(or_zero(ok, rp + (4 * t + g) * kW)));
-    }
-};
-
-// xcol(col): this lane's token (lane % 16) at columns col .. col + 7, zeros
-// past the batch
-template <int NK, class XC>
-__device__ __forceinline__ uint32_t tern_score_mfma(const TernMfmaRows<NK> &tr, XC xcol,
-                                                    const CoefArgs &a, int wr0, int lane)
-{
-    const int n = lane % kTile, g = lane / kTile;
-    f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const u32x4 w = tr.blk[t];
-#pragma unroll
-        for (int j = 0; j < NK; ++j) {
-            const uint32_t W = w[j >> 1];
-            u32x4 wa;
-            wa.x = tern_pair(W, j, 0);
-            wa.y = tern_pair(W, j, 1);
-            wa.z = tern_pair(W, j, 2);
-            wa.w = tern_pair(W, j, 3);
-            acc = mfma16(wa, xcol(j * kColsPerLoad + 8 * (4 * t + g)), acc);
-        }
-    }
-    // lane l holds D[4 g + r][l % 16]: rows 4 g + r of the wave (g < 2), token l % 16
-    uint32_t wmask = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int rw = 4 * g + r;
-        const int row = wr0 + rw;
-        const bool live = rw < kPredRowsPerWave && row < a.d_ff && n < a.nb;
-        const float v = 2.0f * acc[r];
-        if (a.coef && live)
-            a.coef[(size_t)n * a.d_ff + row] = v;
-        const uint64_t m = ballot(live && v > a.thld);
-        const bool act0 = (m & 0xffffull) != 0, act1 = ((m >> 16) & 0xffffull) != 0;
-        if (lane == 0 && wr0 + r < a.d_ff)
-            a.act[wr0 + r] = act0 ? 1 : 0;
-        if (lane == kTile && wr0 + 4 + r < a.d_ff)
-            a.act[wr0 + 4 + r] = act1 ? 1 : 0;
-        wmask |= (act0 && wr0 + r < a.d_ff ? 1u : 0u) << r;
-        wmask |= (act1 && wr0 + 4 + r < a.d_ff ? 1u : 0u) << (4 + r);
-    }
-    return wmask;
-}
-
-// Ternary-predictor coefficient kernel for batches of 1-4: k_coef_pred with
+// Ternary-predictor coefficient kernel for one token: k_coef_pred with
 // the ternary score in place of the latent . B_t one (no latent kernel).
 template <int B, int NK, bool XREG, int NWV = kWavesPerBlock>
 __global__ __launch_bounds__(NWV * kWave) void k_coef_tern(const CoefArgs a)
@@ -1156,82 +780,8 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_tern(const CoefArgs a)
             },
             a, wr0, lane);
     }
-    const uint32_t m = block_share<NWV>(wflag, wmask, wave, lane);
+    const uint32_t m = block_share(wflag, wmask, wave, lane);
     gather_rr<B, NK, XREG, NWV>(a, tok, m, r0, lane);
-}
-
-// LDS bytes of the ternary MFMA kernel: the token copy, which the gather's
-// weight tiles reuse once the scores are in, then the partial sums
-template <int B, int NK>
-__host__ __device__ constexpr size_t tern_mfma_front_u32()
-{
-    constexpr size_t kTiles = (size_t)kWavesPerBlock * WtShape<kWtStepsNarrow>::kWaveElems / 2;
-    return mfma_lds_tokens_u32<B, NK>() > kTiles ? mfma_lds_tokens_u32<B, NK>() : kTiles;
-}
-
-// Ternary-predictor coefficient kernel for batches of 5-8: the ternary score
-// (on MFMA at d_model 4096, tern_score_mfma; v_dot2 otherwise), then the MFMA
-// gather with LDS-staged weight rows.
-template <int B, int NK>
-__global__ __launch_bounds__(kBlock) void k_coef_tern_mfma(const CoefArgs a)
-{
-    // LDS: tokens [B][kStride] (+ zero chunk), overlaid by the weight tiles after
-    // the scores, then the partial sums [4 waves][2][16 x 16]
-    extern __shared__ __align__(16) uint32_t xs[];
-    __shared__ uint32_t wflag[kWavesPerBlock];
-    __shared__ int lrow[kPredRows];
-    using TL = MfmaTokLayout<NK>;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int r0 = blockIdx.x * kPredRows;
-    const int wr0 = r0 + wave * kPredRowsPerWave;
-
-    // the score on MFMA at d_model 4096 (8B layer at 8 tokens: 64.4 -> 58.0 us,
-    // at 5: 54.3 -> 49.0); v_dot2 for the other widths. (At 3-4 tokens, in
-    // k_coef_tern, it measured no faster: 38.5 against 38.2 us at 4.)
-    constexpr bool kMfmaScore = NK == 8;
-    using TR = std::conditional_t<kMfmaScore, TernMfmaRows<8>, TernRows<NK>>;
-    TR tr;
-    tr.issue(a, wr0, lane);
-    MfmaTokens<B, NK> mt;
-    mt.issue(a);
-    __builtin_amdgcn_sched_barrier(0);
-    zero_y(a.y, a.nb * a.d_model);
-    const uint32_t *zchunk = mt.write(xs);
-    __syncthreads();
-
-    uint32_t wmask;
-    if constexpr (kMfmaScore) {
-        const int n = lane % kTile;
-        const uint32_t *xt =
-            n < a.nb ? xs + Tokens<B, NK, false>::opaque_zero() + (size_t)n * TL::kStride : zchunk;
-        // past the batch the zero chunk for every column: a mask on the offset,
-        // not a pointer select per step (the select cost 1.7 us at 8 tokens)
-        const int cm = n < a.nb ? ~0 : 0;
-        wmask = tern_score_mfma<NK>(
-            tr, [&](int col) { return *reinterpret_cast<const u32x4 *>(xt + ((col / 2) & cm)); }, a,
-            wr0, lane);
-    } else {
-        wmask = tern_score<B, NK, true>(
-            tr,
-            [&](int b, int j) {
-                return *reinterpret_cast<const u32x4 *>(xs + Tokens<B, NK, false>::opaque_zero() +
-                                                        (size_t)b * TL::kStride +
-                                                        (j * kColsPerLoad + lane * 8) / 2);
-            },
-            a, wr0, lane);
-    }
-    if (lane == 0)
-        wflag[wave] = wmask;
-    __syncthreads();
-    uint32_t M = 0;
-#pragma unroll
-    for (int v = 0; v < kWavesPerBlock; ++v)
-        M |= wflag[v] << (v * kPredRowsPerWave);
-    (void)zchunk;
-    // (the barrier above ends the token reads: the tiles may overwrite them)
-    gather_mfma_lds<B, NK, false, kWtStepsNarrow>(a, reinterpret_cast<uint16_t *>(xs),
-                           reinterpret_cast<float *>(xs + tern_mfma_front_u32<B, NK>()), lrow, M,
-                           r0, wave, lane);
 }
 
 // latent = x . theta_A for the predictor: one workgroup per row of A_t, the
@@ -1855,6 +1405,14 @@ __device__ __forceinline__ float key_value(uint32_t k, int use_abs)
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
+// v0 + f (v1 - v0) in fp64, each operation rounded (a fused multiply-add would differ
+// from the formula in the last bit)
+__device__ __forceinline__ double interpolate(double v0, double v1, double f)
+{
+#pragma clang fp contract(off)
+    return v0 + f * (v1 - v0);
+}
+
 constexpr int kSelThreads = 1024;
 
 // key of rank r (0-based, ascending) among keys[0..n): 4 passes of 8-bit radix select
@@ -1912,7 +1470,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_quantile(const float *__
     if (lo + 1 < n)
         v1 = (double)key_value(radix_select(keys, n, lo + 1, hist, sh), use_abs);
     if (threadIdx.x == 0)
-        q[blockIdx.x] = v0 + (h - (double)lo) * (v1 - v0);
+        q[blockIdx.x] = interpolate(v0, v1, h - (double)lo);
 }
 
 // The mean of q[0, T) in fp64, added in order by one thread from LDS (a chain of
@@ -2250,7 +1808,7 @@ __device__ __forceinline__ double topk_row(const float *__restrict__ c, int n, i
     }
     const double v0 = (double)key_value(kA, use_abs);
     const double v1 = (double)key_value(two ? kB : kA, use_abs);
-    return v0 + (h - (double)lo) * (v1 - v0);
+    return interpolate(v0, v1, h - (double)lo);
 }
 
 // One workgroup per token. With act set (ideal D-CountDown, |s| keys), the
@@ -2304,71 +1862,6 @@ __device__ __forceinline__ void mono_finish(const CoefArgs &a, const Tokens<B, N
     }
 }
 
-// Per-token threshold and gather for batches of 4-8: a workgroup owns kPredRows neurons; its
-// first kPredRows threads test them against every token's own threshold
-// (|u|, |s| or signed s_hat > q_b, union over the batch) and set act; the
-// active neurons are dealt round-robin to the four waves, which gather W_gate
-// (mono) or W_gate and W_up (pred) and write s; ideal D-CountDown copies s.
-template <int B, int NK, bool XREG, int VARIANT, int NWV = kWavesPerBlock>
-__global__ __launch_bounds__(NWV * kWave) void k_gather_topk(const CoefArgs a, const double *__restrict__ q)
-{
-    extern __shared__ __align__(16) uint32_t xs[];
-    __shared__ uint32_t mask;
-    constexpr bool kGather = VARIANT != kDualIdeal;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    // NWV 8: the first kBlock threads stage the tokens and zero y; all gather
-    const bool first = NWV == kWavesPerBlock || threadIdx.x < kBlock;  // wave-uniform
-    const int r0 = blockIdx.x * kPredRows;
-    Tokens<B, NK, XREG> tok;
-    if constexpr (kGather)
-        if (XREG || first)
-            tok.issue(a.x, a.nb, a.d_model, lane);
-    bool act = false;
-    const int row = r0 + threadIdx.x;
-    if (threadIdx.x < kPredRows && row < a.d_ff) {
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            if (b < a.nb) {
-                const float c = a.coef[(size_t)b * a.d_ff + row];
-                act = act || ((double)(VARIANT == kDualPred ? c : fabsf(c)) > q[b]);
-            }
-        }
-        a.act[row] = act ? 1 : 0;
-        if (VARIANT == kDualIdeal && act)
-#pragma unroll
-            for (int b = 0; b < B; ++b)
-                if (b < a.nb)
-                    a.s[(size_t)b * a.d_ff + row] = a.coef[(size_t)b * a.d_ff + row];
-    }
-    const uint64_t m = ballot(act);
-    if (threadIdx.x == 0)
-        mask = (uint32_t)m;  // the first kPredRows threads are lanes 0..31 of wave 0
-    if (first)
-        zero_y(a.y, a.nb * a.d_model);
-    if constexpr (kGather) {
-        if (first)
-            tok.write(xs);
-        else
-            tok.lds = xs;
-        __syncthreads();
-        uint32_t mm = mask;
-        for (int v = 0; v < wave; ++v)
-            mm &= mm - 1;
-        for (int r = pred_next<NWV>(mm); r >= 0; r = pred_next<NWV>(mm)) {
-            u32x4 wg[NK];
-            const uint16_t *w2 = VARIANT == kCats ? a.Wu : a.Wg;
-            load_row<NK>(wg, w2 + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
-            if constexpr (VARIANT == kMono || VARIANT == kCats) {
-                mono_finish<B, NK, XREG, VARIANT == kCats>(a, tok, wg, r0 + r, lane);
-            } else {
-                u32x4 wu[NK];
-                load_row<NK>(wu, a.Wu + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
-                pred_finish<B, NK, XREG>(a, tok, wg, wu, r0 + r, lane);
-            }
-        }
-    }
-}
-
 // Per-token threshold and gather for batches of 1-2: one wave per neuron.
 // Lane b reads token b's coefficient and threshold; an inactive neuron's wave
 // only writes its flag, an active one issues its token loads with its weight
@@ -2393,10 +1886,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_topk_w(const CoefArgs a, cons
         a.act[row] = act ? 1 : 0;
     if (!act)
         return;
-    if constexpr (VARIANT == kDualIdeal) {
-        if (lane < a.nb)
-            a.s[(size_t)lane * a.d_ff + row] = cb;  // s itself is the coefficient
-    } else {
+    {
         u32x4 wg[NK];
         load_row<NK>(wg, (VARIANT == kCats ? a.Wu : a.Wg) + (size_t)row * a.d_model, a.d_model,
                      lane);
@@ -2627,6 +2117,23 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk_down1(const DownArgs a,
     }
 }
 
+}  // namespace cdk
+
+#include "cd_batch.hpp"
+
+namespace cdk {
+
+// Batches from which the MFMA kernels of cd_batch.hpp run. At 2 tokens half of their
+// products are of empty token columns, and only the ternary predictor gains, whose
+// scores move from v_dot2 to MFMA (4096 x 14336: 29.0 -> 26.2 us; M at 4096 x 11008 28.8
+// against 32.8, dense 49.1 against 49.9, low-rank predictor 28.0 against 29.3).
+constexpr int kBatchMin = 3;
+
+static bool batch_kernels(int variant, int nb)
+{
+    return nb >= kBatchMin || (nb == 2 && variant == kDualTern);
+}
+
 // ------------------------------------------------------------------ launchers
 
 // kernels staging more than 64 KB in LDS opt in to the larger gfx950 limit
@@ -2652,14 +2159,13 @@ int tern_row_words(int d_model)
     return kWave * (nk >= 2 ? nk / 2 : 1);
 }
 
-// tokens live in registers up to a batch of 2, in LDS beyond
 // Whether the coefficient kernels keep the tokens in registers (else one LDS
 // copy per workgroup). Registers hold 4 * B * NK VGPRs of tokens: at two tokens
 // of d_model 8192 that left the two-row and predictor kernels one wave per SIMD,
 // and the LDS copy measured 8-20% faster there (70B shape: ideal D, low-rank and
 // ternary predictors, dense); at one token, and two of d_model <= 4096, the
 // registers are as fast or faster.
-constexpr bool tokens_in_regs(int bt, int nk) { return bt == 1 || (bt == 2 && nk <= 8); }
+constexpr bool tokens_in_regs(int bt, int nk) { return bt == 1 || nk <= 8; }
 
 static size_t token_lds_bytes(int bt, int nk)
 {
@@ -2692,35 +2198,14 @@ void down_grid(int d_model, int d_ff, int bt, int *gc, int *gr, int *rows_per_gr
     *gr = (d_ff + *rows_per_group - 1) / *rows_per_group;
 }
 
-// waves per block of the batch-4 predictor kernels: a block's ~11 active
-// neurons (34% of 32 at 4 tokens) dealt to 8 waves instead of 4 leave each
-// wave one or two row pairs to read instead of about three in a row (8B
-// layer, low-rank: 38.2 -> 36.6 us at 4 tokens, 33.5 -> 32.5 at 3; ternary:
-// 40.6 -> 38.2 and 36.6 -> 34.9). Up to d_model 4096: at 8192 the 8-wave
-// kernels take 192 VGPRs, one block per CU.
-constexpr int kPredWaves4 = 8;
-
 template <int B, int NK, bool XREG, int LCPR>
 static void coef_pred_lcpr(const CoefArgs &a, hipStream_t s)
 {
     const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
     const size_t lat_lds = LatentRegs<B, LCPR>::kRegs ? 0 : (size_t)B * a.d_rank * 4;
-    // MFMA tiles pay off at 8 tokens; at 4 (a block's ~11 active neurons leave a
-    // 16-row tile a third empty) the per-wave v_dot2 gather is faster (8B layer:
-    // 38.2 against 41.5 us with the MFMA kernel)
-    if constexpr (B >= 8) {
-        // weight tiles, then max(latent, 4 x 2 x 16 x 16 partial sums)
-        constexpr int STEPS = LatentRegs<B, LCPR>::kRegs ? kWtStepsWide : kWtStepsNarrow;
-        const size_t lds = (size_t)kWavesPerBlock * WtShape<STEPS>::kWaveElems * 2 +
-                           max(lat_lds, (size_t)kWavesPerBlock * 2 * 256 * 4);
-        allow_lds(k_coef_pred_mfma<B, NK, LCPR>, lds);
-        k_coef_pred_mfma<B, NK, LCPR><<<grid, kBlock, lds, s>>>(a);
-    } else {
-        const size_t lds = (XREG ? 0 : (size_t)B * NK * kColsPerLoad * 2) + lat_lds;
-        constexpr int NWV = (B == 4 && !XREG && NK <= 8) ? kPredWaves4 : kWavesPerBlock;
-        allow_lds(k_coef_pred<B, NK, XREG, LCPR, NWV>, lds);
-        k_coef_pred<B, NK, XREG, LCPR, NWV><<<grid, NWV * kWave, lds, s>>>(a);
-    }
+    const size_t lds = (XREG ? 0 : (size_t)B * NK * kColsPerLoad * 2) + lat_lds;
+    allow_lds(k_coef_pred<B, NK, XREG, LCPR>, lds);
+    k_coef_pred<B, NK, XREG, LCPR><<<grid, kBlock, lds, s>>>(a);
 }
 
 // the predictor kernel is specialised on log2 of the B_t row length in 16-byte chunks
@@ -2745,16 +2230,9 @@ template <int B, int NK, bool XREG>
 static hipError_t coef_tern_launch(const CoefArgs &a, hipStream_t s)
 {
     const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
-    if constexpr (B >= 8) {  // MFMA gather, as for the low-rank predictor
-        const size_t lds = tern_mfma_front_u32<B, NK>() * 4 + (size_t)kWavesPerBlock * 2 * 256 * 4;
-        allow_lds(k_coef_tern_mfma<B, NK>, lds);
-        k_coef_tern_mfma<B, NK><<<grid, kBlock, lds, s>>>(a);
-    } else {
-        const size_t lds = token_lds_bytes(B, NK);
-        constexpr int NWV = (B == 4 && !XREG && NK <= 8) ? kPredWaves4 : kWavesPerBlock;
-        allow_lds(k_coef_tern<B, NK, XREG, NWV>, lds);
-        k_coef_tern<B, NK, XREG, NWV><<<grid, NWV * kWave, lds, s>>>(a);
-    }
+    const size_t lds = XREG ? 0 : (size_t)B * NK * kColsPerLoad * 2;
+    allow_lds(k_coef_tern<B, NK, XREG>, lds);
+    k_coef_tern<B, NK, XREG><<<grid, kBlock, lds, s>>>(a);
     return hipGetLastError();
 }
 
@@ -2793,7 +2271,9 @@ static hipError_t coef_bn(int variant, const CoefArgs &a, hipStream_t s)
     case kDualPred:
         return coef_pred_launch<B, NK, XREG>(a, s);
     case kDualTern:
-        return coef_tern_launch<B, NK, XREG>(a, s);
+        if constexpr (B == 1)  // (from 2 tokens: launch_batch)
+            return coef_tern_launch<B, NK, XREG>(a, s);
+        return hipErrorInvalidValue;
     default:
         return hipErrorInvalidValue;
     }
@@ -2809,21 +2289,15 @@ static hipError_t coef_b(int variant, const CoefArgs &a, hipStream_t s)
     case 4: return coef_bn<B, 4>(variant, a, s);
     case 8: return coef_bn<B, 8>(variant, a, s);
     default:
-        // batch * d_model is capped at 32768 by the plan checks: no 8 x 8192 tile
-        if constexpr (B * 16 <= 64)
-            return coef_bn<B, 16>(variant, a, s);
-        return hipErrorInvalidValue;
+        return coef_bn<B, 16>(variant, a, s);
     }
 }
 
 hipError_t launch_coef(int variant, const CoefArgs &a, hipStream_t s)
 {
-    switch (batch_tile(a.nb)) {
-    case 1: return coef_b<1>(variant, a, s);
-    case 2: return coef_b<2>(variant, a, s);
-    case 4: return coef_b<4>(variant, a, s);
-    default: return coef_b<8>(variant, a, s);
-    }
+    if (batch_kernels(variant, a.nb))
+        return launch_batch(variant, a, nullptr, s);
+    return a.nb == 1 ? coef_b<1>(variant, a, s) : coef_b<2>(variant, a, s);
 }
 
 template <int B>
@@ -2977,43 +2451,12 @@ hipError_t launch_down(const DownArgs &args, hipStream_t s)
 template <int B, int NK>
 static hipError_t gather_topk_bn(int variant, const CoefArgs &a, const double *q, hipStream_t s)
 {
-    constexpr bool XREG = B <= 2;
-    if constexpr (XREG) {
-        const int wgrid = (a.d_ff + kWavesPerBlock - 1) / kWavesPerBlock;
-        switch (variant) {
-        case kMono: k_gather_topk_w<B, NK, kMono><<<wgrid, kBlock, 0, s>>>(a, q); break;
-        case kCats: k_gather_topk_w<B, NK, kCats><<<wgrid, kBlock, 0, s>>>(a, q); break;
-        case kDualIdeal: k_gather_topk_w<B, NK, kDualIdeal><<<wgrid, kBlock, 0, s>>>(a, q); break;
-        case kDualPred: k_gather_topk_w<B, NK, kDualPred><<<wgrid, kBlock, 0, s>>>(a, q); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        // 8 waves per block up to d_model 4096, as in the predictor kernels: each
-        // wave gathers one or two of a block's active neurons instead of about
-        // three in a row (per-token M at 4 tokens 52.4 -> 48.7 us per 7B layer,
-        // low-rank predictor at 8 tokens 74.5 -> 69.9 us per 8B layer)
-        constexpr int GW = NK <= 8 ? 8 : kWavesPerBlock;
-        const size_t lds = token_lds_bytes(B, NK);
-        const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
-        switch (variant) {
-        case kMono:
-            allow_lds(k_gather_topk<B, NK, XREG, kMono, GW>, lds);
-            k_gather_topk<B, NK, XREG, kMono, GW><<<grid, GW * kWave, lds, s>>>(a, q);
-            break;
-        case kCats:
-            allow_lds(k_gather_topk<B, NK, XREG, kCats, GW>, lds);
-            k_gather_topk<B, NK, XREG, kCats, GW><<<grid, GW * kWave, lds, s>>>(a, q);
-            break;
-        case kDualIdeal:
-            k_gather_topk<B, NK, XREG, kDualIdeal><<<grid, kBlock, 0, s>>>(a, q);
-            break;
-        case kDualPred:
-            allow_lds(k_gather_topk<B, NK, XREG, kDualPred, GW>, lds);
-            k_gather_topk<B, NK, XREG, kDualPred, GW><<<grid, GW * kWave, lds, s>>>(a, q);
-            break;
-        default:
-            return hipErrorInvalidValue;
-        }
+    const int grid = (a.d_ff + kWavesPerBlock - 1) / kWavesPerBlock;
+    switch (variant) {
+    case kMono: k_gather_topk_w<B, NK, kMono><<<grid, kBlock, 0, s>>>(a, q); break;
+    case kCats: k_gather_topk_w<B, NK, kCats><<<grid, kBlock, 0, s>>>(a, q); break;
+    case kDualPred: k_gather_topk_w<B, NK, kDualPred><<<grid, kBlock, 0, s>>>(a, q); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
@@ -3027,9 +2470,7 @@ static hipError_t gather_topk_b(int variant, const CoefArgs &a, const double *q,
     case 4: return gather_topk_bn<B, 4>(variant, a, q, s);
     case 8: return gather_topk_bn<B, 8>(variant, a, q, s);
     default:
-        if constexpr (B * 16 <= 64)
-            return gather_topk_bn<B, 16>(variant, a, q, s);
-        return hipErrorInvalidValue;
+        return gather_topk_bn<B, 16>(variant, a, q, s);
     }
 }
 
@@ -3143,12 +2584,9 @@ hipError_t launch_topk(int variant, const CoefArgs &a, double k, double *q, hipS
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ideal)
         return e;
-    switch (batch_tile(a.nb)) {
-    case 1: return gather_topk_b<1>(variant, a, q, s);
-    case 2: return gather_topk_b<2>(variant, a, q, s);
-    case 4: return gather_topk_b<4>(variant, a, q, s);
-    default: return gather_topk_b<8>(variant, a, q, s);
-    }
+    if (a.nb >= kBatchMin)
+        return launch_batch(variant, a, q, s);
+    return a.nb == 1 ? gather_topk_b<1>(variant, a, q, s) : gather_topk_b<2>(variant, a, q, s);
 }
 
 hipError_t launch_export(const int *act, const float *s_rows, int nb, int d_ff, int *idx_dst,
