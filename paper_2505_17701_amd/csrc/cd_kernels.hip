@@ -513,49 +513,18 @@ __device__ __forceinline__ uint32_t block_share(uint32_t *wflag, uint32_t wmask,
 }
 
 // Gather of the wave's share m of the block's active neurons (block base r0):
-// W_gate and W_up rows, s = u * SiLU(g), the next neuron's rows in flight
-// while the current one is reduced.
+// W_gate and W_up rows, s = u * SiLU(g).
 template <int B, int NK, bool XREG, int NW>
 __device__ __forceinline__ void gather_rr(const CoefArgs &a, const Tokens<B, NK, XREG> &tok,
                                           uint32_t m, int r0, int lane)
 {
-    // the next neuron's W_gate + W_up rows in flight while the current one is reduced
-    constexpr bool kPrefetch = NK <= 8 && NW == kWavesPerBlock;
-    int ra = pred_next<NW>(m);
-    if (ra < 0)
-        return;
-    u32x4 ga[NK], ua[NK];
-    load_row<NK>(ga, a.Wg + (size_t)(r0 + ra) * a.d_model, a.d_model, lane);
-    load_row<NK>(ua, a.Wu + (size_t)(r0 + ra) * a.d_model, a.d_model, lane);
-    if constexpr (kPrefetch) {
-        u32x4 gb[NK], ub[NK];
-        for (;;) {
-            const int rb = pred_next<NW>(m);
-            if (rb >= 0) {
-                load_row<NK>(gb, a.Wg + (size_t)(r0 + rb) * a.d_model, a.d_model, lane);
-                load_row<NK>(ub, a.Wu + (size_t)(r0 + rb) * a.d_model, a.d_model, lane);
-            }
-            pred_finish<B, NK, XREG>(a, tok, ga, ua, r0 + ra, lane);
-            if (rb < 0)
-                break;
-            ra = pred_next<NW>(m);
-            if (ra >= 0) {
-                load_row<NK>(ga, a.Wg + (size_t)(r0 + ra) * a.d_model, a.d_model, lane);
-                load_row<NK>(ua, a.Wu + (size_t)(r0 + ra) * a.d_model, a.d_model, lane);
-            }
-            pred_finish<B, NK, XREG>(a, tok, gb, ub, r0 + rb, lane);
-            if (ra < 0)
-                break;
-        }
-    } else {
-        for (;;) {
-            pred_finish<B, NK, XREG>(a, tok, ga, ua, r0 + ra, lane);
-            ra = pred_next<NW>(m);
-            if (ra < 0)
-                break;
-            load_row<NK>(ga, a.Wg + (size_t)(r0 + ra) * a.d_model, a.d_model, lane);
-            load_row<NK>(ua, a.Wu + (size_t)(r0 + ra) * a.d_model, a.d_model, lane);
-        }
+    int r = pred_next<NW>(m);
+    while (r >= 0) {
+        u32x4 g[NK], u[NK];
+        load_row<NK>(g, a.Wg + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
+        load_row<NK>(u, a.Wu + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
+        pred_finish<B, NK, XREG>(a, tok, g, u, r0 + r, lane);
+        r = pred_next<NW>(m);
     }
 }
 
@@ -565,10 +534,9 @@ __device__ __forceinline__ void gather_rr(const CoefArgs &a, const Tokens<B, NK,
 // copy) and the latent.
 // Each wave scores its rows (s_hat = latent . B_t[row], signed threshold,
 // union over the batch); the block's active neurons are then dealt
-// round-robin to the four waves, which gather their W_gate and W_up rows
-// (for 1-2 tokens the next row's loads in flight while the current one is
-// reduced) and write s = u * SiLU(g).
-template <int B, int NK, bool XREG, int LCPR, int NWV = kWavesPerBlock>
+// round-robin to the NWV waves, which gather their W_gate and W_up rows and
+// write s = u * SiLU(g).
+template <int B, int NK, bool XREG, int LCPR, int NWV>
 __global__ __launch_bounds__(NWV * kWave) void k_coef_pred(const CoefArgs a)
 {
     extern __shared__ __align__(16) uint32_t xs[];  // [tokens [B][NK * 256]], latent [B][d_rank]
@@ -741,7 +709,7 @@ __device__ __forceinline__ uint32_t tern_score(const TernRows<NK> &t, XF xget, c
 
 // Ternary-predictor coefficient kernel for one token: k_coef_pred with
 // the ternary score in place of the latent . B_t one (no latent kernel).
-template <int B, int NK, bool XREG, int NWV = kWavesPerBlock>
+template <int B, int NK, bool XREG, int NWV>
 __global__ __launch_bounds__(NWV * kWave) void k_coef_tern(const CoefArgs a)
 {
     extern __shared__ __align__(16) uint32_t xs[];  // tokens [B][NK * 256] (LDS path)
@@ -2198,41 +2166,54 @@ void down_grid(int d_model, int d_ff, int bt, int *gc, int *gr, int *rows_per_gr
     *gr = (d_ff + *rows_per_group - 1) / *rows_per_group;
 }
 
-template <int B, int NK, bool XREG, int LCPR>
+// Waves per block of the predictor kernels, and where they keep the tokens. Up to
+// d_model 4096: 8 waves, of which four score the block's 32 neurons and all gather, with
+// the tokens in one LDS copy. A block's active neurons (3 on average at 90% sparsity, 8-10
+// in the fullest blocks, which end the kernel) are then one row pair per wave instead of two
+// or three in turn, and without tokens and a second neuron's rows in registers (185 of
+// them) two such blocks fit a CU: 4096 x 14336 at 1 token 19.3 -> 19.0 us (ternary 20.4 ->
+// 19.4), at 2 tokens 28.0 -> 27.4; 16 waves 19.9, 4 waves with the LDS copy 19.7. Past
+// 4096 columns a row pair alone takes 128 registers: 4 waves, tokens as tokens_in_regs.
+constexpr int pred_waves(int nk) { return nk <= 8 ? 8 : kWavesPerBlock; }
+constexpr bool pred_tokens_in_regs(int bt, int nk) { return nk > 8 && tokens_in_regs(bt, nk); }
+
+template <int B, int NK, int LCPR>
 static void coef_pred_lcpr(const CoefArgs &a, hipStream_t s)
 {
     const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
     const size_t lat_lds = LatentRegs<B, LCPR>::kRegs ? 0 : (size_t)B * a.d_rank * 4;
-    const size_t lds = (XREG ? 0 : (size_t)B * NK * kColsPerLoad * 2) + lat_lds;
-    allow_lds(k_coef_pred<B, NK, XREG, LCPR>, lds);
-    k_coef_pred<B, NK, XREG, LCPR><<<grid, kBlock, lds, s>>>(a);
+    constexpr bool XR = pred_tokens_in_regs(B, NK);
+    const size_t lds = (XR ? 0 : (size_t)B * NK * kColsPerLoad * 2) + lat_lds;
+    allow_lds(k_coef_pred<B, NK, XR, LCPR, pred_waves(NK)>, lds);
+    k_coef_pred<B, NK, XR, LCPR, pred_waves(NK)><<<grid, pred_waves(NK) * kWave, lds, s>>>(a);
 }
 
 // the predictor kernel is specialised on log2 of the B_t row length in 16-byte chunks
-template <int B, int NK, bool XREG>
+template <int B, int NK>
 static hipError_t coef_pred_launch(const CoefArgs &a, hipStream_t s)
 {
     switch (a.d_rank) {
-    case 8: coef_pred_lcpr<B, NK, XREG, 0>(a, s); break;
-    case 16: coef_pred_lcpr<B, NK, XREG, 1>(a, s); break;
-    case 32: coef_pred_lcpr<B, NK, XREG, 2>(a, s); break;
-    case 64: coef_pred_lcpr<B, NK, XREG, 3>(a, s); break;
-    case 128: coef_pred_lcpr<B, NK, XREG, 4>(a, s); break;
-    case 256: coef_pred_lcpr<B, NK, XREG, 5>(a, s); break;
-    case 512: coef_pred_lcpr<B, NK, XREG, 6>(a, s); break;
-    case 1024: coef_pred_lcpr<B, NK, XREG, 7>(a, s); break;
+    case 8: coef_pred_lcpr<B, NK, 0>(a, s); break;
+    case 16: coef_pred_lcpr<B, NK, 1>(a, s); break;
+    case 32: coef_pred_lcpr<B, NK, 2>(a, s); break;
+    case 64: coef_pred_lcpr<B, NK, 3>(a, s); break;
+    case 128: coef_pred_lcpr<B, NK, 4>(a, s); break;
+    case 256: coef_pred_lcpr<B, NK, 5>(a, s); break;
+    case 512: coef_pred_lcpr<B, NK, 6>(a, s); break;
+    case 1024: coef_pred_lcpr<B, NK, 7>(a, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-template <int B, int NK, bool XREG>
+template <int B, int NK>
 static hipError_t coef_tern_launch(const CoefArgs &a, hipStream_t s)
 {
     const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
-    const size_t lds = XREG ? 0 : (size_t)B * NK * kColsPerLoad * 2;
-    allow_lds(k_coef_tern<B, NK, XREG>, lds);
-    k_coef_tern<B, NK, XREG><<<grid, kBlock, lds, s>>>(a);
+    constexpr bool XR = pred_tokens_in_regs(B, NK);
+    const size_t lds = XR ? 0 : (size_t)B * NK * kColsPerLoad * 2;
+    allow_lds(k_coef_tern<B, NK, XR, pred_waves(NK)>, lds);
+    k_coef_tern<B, NK, XR, pred_waves(NK)><<<grid, pred_waves(NK) * kWave, lds, s>>>(a);
     return hipGetLastError();
 }
 
@@ -2269,10 +2250,10 @@ static hipError_t coef_bn(int variant, const CoefArgs &a, hipStream_t s)
         k_coef_dual<B, NK, XREG, true><<<grid, kBlock, lds, s>>>(a);
         break;
     case kDualPred:
-        return coef_pred_launch<B, NK, XREG>(a, s);
+        return coef_pred_launch<B, NK>(a, s);
     case kDualTern:
         if constexpr (B == 1)  // (from 2 tokens: launch_batch)
-            return coef_tern_launch<B, NK, XREG>(a, s);
+            return coef_tern_launch<B, NK>(a, s);
         return hipErrorInvalidValue;
     default:
         return hipErrorInvalidValue;
