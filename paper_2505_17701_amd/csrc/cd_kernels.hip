@@ -1128,10 +1128,9 @@ constexpr int kDownScanPasses = 2;
 // MFMA whose output columns are 8 j + e, so the loaded data needs no LDS
 // transpose. S enters as bf16 hi + lo (s - hi rounded again), two MFMAs per
 // operand, so each product keeps about 16 mantissa bits.
-template <int BT>
+template <int BT, int T>
 __global__ __launch_bounds__(kBlock) void k_down_mfma(const DownArgs a)
 {
-    constexpr int T = kDownScanPasses;
     extern __shared__ __align__(16) int dsm[];
     __shared__ int wcnt[T][kWavesPerBlock];
     const int cap = a.rows_per_group;
@@ -1150,26 +1149,32 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const DownArgs a)
     // flags and s of four consecutive neurons per thread (16-byte loads: a
     // quarter of the load instructions of one neuron per thread, which at
     // batch 8 took about 1.4 us more per call); the list stays ascending
-    int f[T][4], below[T];
-    float sv[T][BT][4];
+    int4 av[T];
+    float4 sv[T][BT];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int row = r0 + t * 4 * kBlock + 4 * threadIdx.x;
         const bool ok = t * 4 * kBlock < cap && row < r1;  // r0, r1 multiples of 4 (host)
-        const int4 av = *or_zero(ok, reinterpret_cast<const int4 *>(a.act + row));
-        f[t][0] = av.x != 0;
-        f[t][1] = av.y != 0;
-        f[t][2] = av.z != 0;
-        f[t][3] = av.w != 0;
+        av[t] = *or_zero(ok, reinterpret_cast<const int4 *>(a.act + row));
+    }
+    __builtin_amdgcn_sched_barrier(0);  // the flags first: the list needs nothing else
 #pragma unroll
-        for (int b = 0; b < BT; ++b) {
-            const float4 v =
+    for (int t = 0; t < T; ++t) {
+        const int row = r0 + t * 4 * kBlock + 4 * threadIdx.x;
+        const bool ok = t * 4 * kBlock < cap && row < r1;
+#pragma unroll
+        for (int b = 0; b < BT; ++b)
+            sv[t][b] =
                 *or_zero(ok && b < a.nb, reinterpret_cast<const float4 *>(a.s + (size_t)b * a.d_ff + row));
-            sv[t][b][0] = v.x;
-            sv[t][b][1] = v.y;
-            sv[t][b][2] = v.z;
-            sv[t][b][3] = v.w;
-        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    int f[T][4], below[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        f[t][0] = av[t].x != 0;
+        f[t][1] = av[t].y != 0;
+        f[t][2] = av[t].z != 0;
+        f[t][3] = av[t].w != 0;
         int tot = 0;
         below[t] = 0;
 #pragma unroll
@@ -1185,43 +1190,30 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const DownArgs a)
         zrow[threadIdx.x] = 0u;
     __syncthreads();
     int nl = 0;
+    int pos0[T];  // list position of this thread's first active neuron of pass t
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         int pos = nl + below[t];
         for (int v = 0; v < wave; ++v)
             pos += wcnt[t][v];
+        pos0[t] = pos;
         const int row = r0 + t * 4 * kBlock + 4 * threadIdx.x;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (f[t][k]) {
-                lrow[pos] = row + k;
-#pragma unroll
-                for (int b = 0; b < BT; ++b) {
-                    const __bf16 h = (__bf16)sv[t][b][k];
-                    const __bf16 l = (__bf16)(sv[t][b][k] - (float)h);
-                    shi[b * capp + pos] = __builtin_bit_cast(uint16_t, h);
-                    slo[b * capp + pos] = __builtin_bit_cast(uint16_t, l);
-                }
-                ++pos;
-            }
+            if (f[t][k])
+                lrow[pos++] = row + k;
         nl += wcnt[t][0] + wcnt[t][1] + wcnt[t][2] + wcnt[t][3];
     }
-    // zero coefficients (and a valid row) for the padding of the last step
-    const int nlp = (nl + 31) & ~31;
-    for (int p = nl + threadIdx.x; p < nlp; p += kBlock) {
-        lrow[p] = r0;
-#pragma unroll
-        for (int b = 0; b < BT; ++b) {
-            shi[b * capp + p] = 0;
-            slo[b * capp + p] = 0;
-        }
-    }
-    __syncthreads();
     if (nl == 0) {  // uniform for the workgroup
         if (a.part)
             zero_part(a, g, c * kWc, kWc);
         return;
     }
+    // a valid row for the padding of the last step
+    const int nlp = (nl + 31) & ~31;
+    for (int p = nl + threadIdx.x; p < nlp; p += kBlock)
+        lrow[p] = r0;
+    __syncthreads();
 
     const int j = lane % 16, q = lane / 16;
     const int col = c * kWc + j * 8;
@@ -1235,13 +1227,14 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const DownArgs a)
 
     u32x4 cur[8], nxt[8];
     auto load_step = [&](u32x4 (&w)[8], int p0) {
+        const int p = p0 + 8 * q;
+        const int4 ra = *reinterpret_cast<const int4 *>(lrow + p);
+        const int4 rb = *reinterpret_cast<const int4 *>(lrow + p + 4);
+        const int rows[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int p = p0 + 8 * q + r;
-            w[r] = zero16();
-            if (p < nl && colok)
-                w[r] = load16_stream(a.Wd + (size_t)lrow[p] * a.d_model + col);
-        }
+        for (int r = 0; r < 8; ++r)  // (padding reads zeros: 0 x a NaN weight would not be 0)
+            w[r] = load16_stream(
+                or_zero(p + r < nl && colok, a.Wd + (size_t)rows[r] * a.d_model + col));
     };
     auto consume = [&](const u32x4 (&w)[8], int p0) {
         const int pa = p0 + 8 * q;
@@ -1265,8 +1258,36 @@ __global__ __launch_bounds__(kBlock) void k_down_mfma(const DownArgs a)
     // this wave's steps start at positions wave * kStep + k * 4 * kStep
     constexpr int kStride = kWavesPerBlock * kStep;
     const int pw = wave * kStep;
-    if (pw < nl) {  // uniform per wave
+    // The first step's rows are on their way while the coefficients go into LDS as bf16
+    // hi and lo (zeros for the padding).
+    if (pw < nl)  // uniform per wave
         load_step(cur, pw);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        int pos = pos0[t];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (f[t][k]) {
+#pragma unroll
+                for (int b = 0; b < BT; ++b) {
+                    const float v = k == 0 ? sv[t][b].x : k == 1 ? sv[t][b].y : k == 2 ? sv[t][b].z : sv[t][b].w;
+                    const __bf16 h = (__bf16)v;
+                    const __bf16 l = (__bf16)(v - (float)h);
+                    shi[b * capp + pos] = __builtin_bit_cast(uint16_t, h);
+                    slo[b * capp + pos] = __builtin_bit_cast(uint16_t, l);
+                }
+                ++pos;
+            }
+    }
+    for (int p = nl + threadIdx.x; p < nlp; p += kBlock)
+#pragma unroll
+        for (int b = 0; b < BT; ++b) {
+            shi[b * capp + p] = 0;
+            slo[b * capp + p] = 0;
+        }
+    __syncthreads();
+    if (pw < nl) {  // uniform per wave
         for (int p0 = pw; p0 < nl; p0 += 2 * kStride) {
             const bool more = p0 + kStride < nl;  // uniform
             if (more)
@@ -2405,13 +2426,11 @@ hipError_t launch_down(const DownArgs &args, hipStream_t s)
         down_grid_mfma(a.d_model, a.d_ff, bt, &a.gc, &a.gr, &a.rows_per_group);
         const size_t lds = down_mfma_lds_bytes(a.rows_per_group, bt);
         const int grid = a.gc * a.gr;
-        if (bt == 4) {
-            allow_lds(k_down_mfma<4>, lds);
-            k_down_mfma<4><<<grid, kBlock, lds, s>>>(a);
-        } else {
-            allow_lds(k_down_mfma<8>, lds);
-            k_down_mfma<8><<<grid, kBlock, lds, s>>>(a);
-        }
+        const bool one = a.rows_per_group <= 4 * kBlock;  // one pass over the flags
+        if (bt == 4)
+            (one ? k_down_mfma<4, 1> : k_down_mfma<4, 2>)<<<grid, kBlock, lds, s>>>(a);
+        else
+            (one ? k_down_mfma<8, 1> : k_down_mfma<8, 2>)<<<grid, kBlock, lds, s>>>(a);
         const hipError_t e = hipGetLastError();
         return e != hipSuccess ? e : reduce_parts(a, s);
     }
