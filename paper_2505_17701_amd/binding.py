@@ -95,6 +95,30 @@ def _check(status: int, what: str) -> None:
         raise CountdownError(status, what)
 
 
+# A call of a small layer is bound by this module: 256 x 688 at one token took 15.4 us a
+# call, 7 of them on the GPU. So torch and its dtypes are looked up once (the module can be
+# imported without torch), each operand is checked and its pointer taken in one step, and
+# the current stream's handle is read without building a Stream object.
+_torch = None
+
+
+def _use_torch():
+    global _torch, _BF16, _F32, _raw_stream
+    import torch
+
+    _BF16, _F32 = torch.bfloat16, torch.float32
+    try:  # (device index) -> handle of its current stream
+        raw, device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+
+        def _raw_stream():
+            return raw(device())
+    except AttributeError:
+        def _raw_stream():
+            return torch.cuda.current_stream().cuda_stream
+    _torch = torch
+    return torch
+
+
 def _ptr(t) -> int | None:
     """Device pointer of a torch tensor (None -> NULL)."""
     if t is None:
@@ -108,24 +132,29 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int | None:
     if stream is None:
-        import torch
-
-        return torch.cuda.current_stream().cuda_stream
+        if _torch is None:
+            _use_torch()
+        return _raw_stream()
     return int(stream) if not hasattr(stream, "cuda_stream") else stream.cuda_stream
 
 
-def _bf16(t):
-    import torch
-
-    if t is not None and t.dtype != torch.bfloat16:
+def _bf16(t) -> int | None:
+    """Device pointer of a bfloat16 tensor (None -> NULL)."""
+    if t is None:
+        return None
+    if _torch is None:
+        _use_torch()
+    if t.dtype is not _BF16:
         raise TypeError(f"expected a bfloat16 tensor, got {t.dtype}")
-    return t
+    if t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
+    return _ptr(t)  # raises
 
 
 def _f32(t):
-    import torch
-
-    if t.dtype != torch.float32:
+    if _torch is None:
+        _use_torch()
+    if t.dtype is not _F32:
         raise TypeError(f"expected a float32 tensor, got {t.dtype}")
     return t
 
@@ -174,20 +203,24 @@ def countdown_plan_destroy(plan: Plan) -> None:
 
 def _shape(t, shape, name):
     """ValueError unless ``t`` (None is skipped) has exactly ``shape``."""
-    if t is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
+    if t is not None and t.shape != shape:
+        raise ValueError(f"{name} must have shape {shape}, got {tuple(t.shape)}")
 
 
 def _layer_shapes(plan, x, W_gate=None, W_up=None, W_down=None, A_t=None, B_t=None,
                   theta_packed=None):
     """Check a call's tensors against the plan before any pointer is taken: the C ABI
     sees only pointers, and the kernels read exactly these extents."""
-    if x.dim() != 2 or x.shape[1] != plan.d_model:
-        raise ValueError(f"x must be [B, {plan.d_model}], got {tuple(x.shape)}")
-    for t, name in ((W_gate, "W_gate"), (W_up, "W_up"), (W_down, "W_down")):
-        _shape(t, (plan.d_ff, plan.d_model), name)
-    _shape(A_t, (plan.d_rank, plan.d_model), "A_t")
-    _shape(B_t, (plan.d_ff, plan.d_rank), "B_t")
+    xs = x.shape
+    if len(xs) != 2 or xs[1] != plan.d_model:
+        raise ValueError(f"x must be [B, {plan.d_model}], got {tuple(xs)}")
+    shape = (plan.d_ff, plan.d_model)
+    _shape(W_gate, shape, "W_gate")
+    _shape(W_up, shape, "W_up")
+    _shape(W_down, shape, "W_down")
+    if A_t is not None or B_t is not None:
+        _shape(A_t, (plan.d_rank, plan.d_model), "A_t")
+        _shape(B_t, (plan.d_ff, plan.d_rank), "B_t")
     if theta_packed is not None:
         words = countdown_ternary_words(plan.d_model, plan.d_ff)
         if theta_packed.numel() * theta_packed.element_size() != 4 * words:
@@ -196,11 +229,11 @@ def _layer_shapes(plan, x, W_gate=None, W_up=None, W_down=None, A_t=None, B_t=No
 
 
 def _out(plan: Plan, x, y):
-    import torch
-
     B = x.shape[0]
     if y is None:
-        y = torch.empty((B, plan.d_model), dtype=torch.float32, device=x.device)
+        if _torch is None:
+            _use_torch()
+        return B, _torch.empty((B, plan.d_model), dtype=_F32, device=x.device)
     _shape(y, (B, plan.d_model), "y")
     return B, _f32(y)
 
@@ -210,8 +243,8 @@ def countdown_ffn_mono(plan: Plan, x, W_gate, W_up, W_down, thld: float, y=None,
     _layer_shapes(plan, x, W_gate, W_up, W_down)
     B, y = _out(plan, x, y)
     _check(load_library().countdown_ffn_mono(
-        plan.handle, _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), float(thld), _ptr(y), _stream(stream)), "countdown_ffn_mono")
+        plan.handle, _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), float(thld), _ptr(y), _stream(stream)), "countdown_ffn_mono")
     plan.last_batch = B
     return y
 
@@ -230,7 +263,7 @@ def countdown_ffn_mono_noalloc(x, W_gate, W_up, W_down, thld: float, y, stream=N
         _shape(t, (dff, dm), name)
     _shape(_f32(y), (B, dm), "y")
     _check(load_library().countdown_ffn_mono_noalloc(
-        _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)), _ptr(_bf16(W_down)), dm, dff,
+        _bf16(x), B, _bf16(W_gate), _bf16(W_up), _bf16(W_down), dm, dff,
         float(thld), _ptr(y), _stream(stream)), "countdown_ffn_mono_noalloc")
     return y
 
@@ -241,8 +274,8 @@ def countdown_ffn_dual(plan: Plan, x, W_gate, W_up, W_down, thld: float, A_t=Non
     _layer_shapes(plan, x, W_gate, W_up, W_down, A_t, B_t)
     B, y = _out(plan, x, y)
     _check(load_library().countdown_ffn_dual(
-        plan.handle, _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), _ptr(_bf16(A_t)), _ptr(_bf16(B_t)), float(thld), _ptr(y),
+        plan.handle, _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), _bf16(A_t), _bf16(B_t), float(thld), _ptr(y),
         _stream(stream)), "countdown_ffn_dual")
     plan.last_batch = B
     return y
@@ -253,8 +286,8 @@ def countdown_ffn_cats(plan: Plan, x, W_gate, W_up, W_down, thld: float, y=None,
     _layer_shapes(plan, x, W_gate, W_up, W_down)
     B, y = _out(plan, x, y)
     _check(load_library().countdown_ffn_cats(
-        plan.handle, _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), float(thld), _ptr(y), _stream(stream)), "countdown_ffn_cats")
+        plan.handle, _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), float(thld), _ptr(y), _stream(stream)), "countdown_ffn_cats")
     plan.last_batch = B
     return y
 
@@ -271,8 +304,8 @@ def countdown_ffn_topk(plan: Plan, variant: int, x, W_gate, W_up, W_down, k: flo
     if thld_out is not None and (thld_out.dtype != torch.float64 or thld_out.numel() < B):
         raise ValueError("thld_out must be a float64 device tensor with at least B entries")
     _check(load_library().countdown_ffn_topk(
-        plan.handle, int(variant), _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), _ptr(_bf16(A_t)), _ptr(_bf16(B_t)), float(k), _ptr(thld_out),
+        plan.handle, int(variant), _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), _bf16(A_t), _bf16(B_t), float(k), _ptr(thld_out),
         _ptr(y), _stream(stream)), "countdown_ffn_topk")
     plan.last_batch = B
     return y
@@ -296,8 +329,8 @@ def countdown_ffn_residual(plan: Plan, variant: int, h_in, y_prev, h_out, x_out,
     _layer_shapes(plan, x_out, W_gate, W_up, W_down, A_t, B_t)
     _check(load_library().countdown_ffn_residual(
         plan.handle, int(variant), _ptr(h_in), _ptr(y_prev), _ptr(h_out), float(eps),
-        _ptr(_bf16(x_out)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)), _ptr(_bf16(W_down)),
-        _ptr(_bf16(A_t)), _ptr(_bf16(B_t)), float(thld), _ptr(y), _stream(stream)),
+        _bf16(x_out), B, _bf16(W_gate), _bf16(W_up), _bf16(W_down),
+        _bf16(A_t), _bf16(B_t), float(thld), _ptr(y), _stream(stream)),
         "countdown_ffn_residual")
     plan.last_batch = B
     return y
@@ -308,8 +341,8 @@ def countdown_ffn_dense(plan: Plan, x, W_gate, W_up, W_down, y=None, stream=None
     _layer_shapes(plan, x, W_gate, W_up, W_down)
     B, y = _out(plan, x, y)
     _check(load_library().countdown_ffn_dense(
-        plan.handle, _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), _ptr(y), _stream(stream)), "countdown_ffn_dense")
+        plan.handle, _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), _ptr(y), _stream(stream)), "countdown_ffn_dense")
     plan.last_batch = B
     return y
 
@@ -324,8 +357,8 @@ def countdown_calibrate(plan: Plan, variant: int, X, k: float, W_gate=None, W_up
     thld = torch.empty(1, dtype=torch.float32, device=X.device)
     q = torch.empty(T, dtype=torch.float64, device=X.device)
     _check(load_library().countdown_calibrate(
-        plan.handle, int(variant), _ptr(_bf16(X)), T, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(A_t)), _ptr(_bf16(B_t)), float(k), _ptr(thld), _ptr(q), _stream(stream)),
+        plan.handle, int(variant), _bf16(X), T, _bf16(W_gate), _bf16(W_up),
+        _bf16(A_t), _bf16(B_t), float(k), _ptr(thld), _ptr(q), _stream(stream)),
         "countdown_calibrate")
     return thld, q
 
@@ -366,8 +399,8 @@ def countdown_ffn_tern(plan: Plan, x, W_gate, W_up, W_down, theta_packed, thld: 
     _layer_shapes(plan, x, W_gate, W_up, W_down, theta_packed=theta_packed)
     B, y = _out(plan, x, y)
     _check(load_library().countdown_ffn_tern(
-        plan.handle, _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), _ptr(_u32(theta_packed)), float(thld), _ptr(y), _stream(stream)),
+        plan.handle, _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), _ptr(_u32(theta_packed)), float(thld), _ptr(y), _stream(stream)),
         "countdown_ffn_tern")
     plan.last_batch = B
     return y
@@ -383,8 +416,8 @@ def countdown_ffn_tern_topk(plan: Plan, x, W_gate, W_up, W_down, theta_packed, k
     if thld_out is not None and (thld_out.dtype != torch.float64 or thld_out.numel() < B):
         raise ValueError("thld_out must be a float64 device tensor with at least B entries")
     _check(load_library().countdown_ffn_tern_topk(
-        plan.handle, _ptr(_bf16(x)), B, _ptr(_bf16(W_gate)), _ptr(_bf16(W_up)),
-        _ptr(_bf16(W_down)), _ptr(_u32(theta_packed)), float(k), _ptr(thld_out), _ptr(y),
+        plan.handle, _bf16(x), B, _bf16(W_gate), _bf16(W_up),
+        _bf16(W_down), _ptr(_u32(theta_packed)), float(k), _ptr(thld_out), _ptr(y),
         _stream(stream)), "countdown_ffn_tern_topk")
     plan.last_batch = B
     return y
@@ -399,7 +432,7 @@ def countdown_calibrate_tern(plan: Plan, X, theta_packed, k: float, stream=None)
     thld = torch.empty(1, dtype=torch.float32, device=X.device)
     q = torch.empty(T, dtype=torch.float64, device=X.device)
     _check(load_library().countdown_calibrate_tern(
-        plan.handle, _ptr(_bf16(X)), T, _ptr(_u32(theta_packed)), float(k), _ptr(thld), _ptr(q),
+        plan.handle, _bf16(X), T, _ptr(_u32(theta_packed)), float(k), _ptr(thld), _ptr(q),
         _stream(stream)), "countdown_calibrate_tern")
     return thld, q
 
