@@ -243,7 +243,7 @@ cd_status run_ffn(cd_plan *p, int variant, const uint16_t *x, int B, const uint1
                 return st;
         }
         const cdk::CoefArgs ca = coef_args(p, x, B, Wg, Wu, Bt, thld, y, Tp);
-        st = launched(cdk::launch_coef(kernel_variant(variant), ca, s));
+        st = launched(cdk::launch_coef(kernel_variant(variant), ca, false, s));
         if (st != CD_OK)
             return st;
         keep_state(p, B, false);
@@ -310,7 +310,7 @@ cd_status run_ffn_residual(cd_plan *p, int variant, const float *h_in, const flo
         if (st != CD_OK)
             return st;
         const cdk::CoefArgs ca = coef_args(p, x_out, B, Wg, Wu, Bt, thld, y);
-        st = launched(cdk::launch_coef(kernel_variant(variant), ca, s));
+        st = launched(cdk::launch_coef(kernel_variant(variant), ca, true, s));
         if (st != CD_OK)
             return st;
         keep_state(p, B, false);
@@ -361,7 +361,7 @@ cd_status run_ffn_topk(cd_plan *p, int variant, const uint16_t *x, int B, const 
         // dense coefficients of every neuron (threshold +inf: nothing is gathered yet)
         cdk::CoefArgs ca = coef_args(p, x, B, Wg, Wu, Bt, INFINITY, y, Tp);
         ca.coef = p->coef;
-        st = launched(cdk::launch_coef(kernel_variant(variant), ca, s));
+        st = launched(cdk::launch_coef(kernel_variant(variant), ca, false, s));
         if (st != CD_OK)
             return st;
         double *q = thld_out ? thld_out : p->q;
@@ -683,7 +683,7 @@ cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uin
                                     INFINITY, a.scratch, Tp);  // y: zeroed, not read
         c.coef = a.coef;
         if (st == CD_OK)
-            st = launched(cdk::launch_coef(variant, c, s));
+            st = launched(cdk::launch_coef(variant, c, false, s));
         if (st == CD_OK)
             st = launched(cdk::launch_select(a.coef, p->d_ff, p->d_ff, T, pred || tern ? 0 : 1, k,
                                              q, s));

@@ -60,7 +60,7 @@ int batch_tile(int B);        // 1, 2, 4 or 8
 int col_tile(int d_model);    // chunks of 512 columns: 1, 2, 4, 8 or 16
 size_t down_lds_bytes(int rows_per_group, int bt);
 
-hipError_t launch_coef(int variant, const CoefArgs &a, hipStream_t s);
+hipError_t launch_coef(int variant, const CoefArgs &a, bool stacked, hipStream_t s);
 hipError_t launch_latent(const uint16_t *x, int nb, const uint16_t *At, int d_model, int d_rank,
                          float *lat, hipStream_t s);
 hipError_t launch_down(const DownArgs &a, hipStream_t s);

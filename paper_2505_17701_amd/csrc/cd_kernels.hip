@@ -583,6 +583,253 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_pred(const CoefArgs a)
     gather_rr<B, NK, XREG, NWV>(a, tok, m, r0, lane);
 }
 
+// ----------------- MFMA gather for 5-8 tokens of a residual stack (see launch_coef)
+// For 5-8 tokens the gathered products are small dense contractions: a tile
+// of 16 active neurons times the batch, on v_mfma_f32_16x16x32_bf16. Lane
+// l = i + 16 g (i = l % 16, g = l / 16) supplies row i of the tile (A operand)
+// and token i of the batch (B operand, zero for i >= B), each with the 8
+// columns 32 s + 8 g + [0, 8) of step s, so both operands use the same
+// column order. The four waves take a quarter of the steps each and add
+// their 16 x 16 partial sums in LDS; lane l holds D[4 (l / 16) + r][l % 16].
+
+// MFMA gather with the weight rows staged in LDS. Loads in the MFMA operand
+// layout (16 rows x 64 B per instruction) reach about 60% of the HBM rate of
+// row-contiguous loads on gathered rows (measured), so a wave loads each
+// batch of STEPS steps (32 columns each) of its tile's 16 W_gate and W_up rows
+// with 4 STEPS lanes on each row's piece (256 B of a row per load at 4 steps,
+// 512 B at 8), writes them to its own LDS tile (rows padded by 16 B) and
+// reads the A operands back; the token operand (L2-resident) is loaded with
+// the batch.
+template <int STEPS>
+struct WtShape {
+    static constexpr int kCols = STEPS * 32;              // columns of a batch
+    static constexpr int kStride = kCols + 8;             // bf16 per tile row
+    static constexpr int kWaveElems = 2 * kTile * kStride;  // bf16 per wave: W_gate and W_up tiles
+    static constexpr int kLanesPerRow = kCols / 8;        // lanes on one row's piece
+    static constexpr int kRowsPerLoad = kWave / kLanesPerRow;
+    static constexpr int kLoads = kTile / kRowsPerLoad;   // loads per lane and matrix
+};
+
+// batch widths: the low-rank kernel's 256 columns with one batch in flight
+// per wave measured 1-1.5% faster at 5-8 tokens than 128 columns with two in
+// flight (two 256-column batches take 254 VGPRs, one wave per SIMD); the
+// ternary kernel, and the low-rank one at rank 1024 (latent in LDS), keep
+// 128-column batches, two in flight (with 256 columns the ternary layer took
+// 80.7 against 64.4 us at 8 tokens)
+constexpr int kWtStepsWide = 8;
+constexpr int kWtStepsNarrow = 4;
+
+template <int STEPS>
+struct WtBatch {
+    using W = WtShape<STEPS>;
+    u32x4 w[2 * W::kLoads];  // W_gate rows kRowsPerLoad q + lane / kLanesPerRow, then W_up
+    u32x4 x[STEPS];
+};
+
+template <int STEPS>
+__device__ __forceinline__ void wt_load(WtBatch<STEPS> &bt, const CoefArgs &a,
+                                        const int (&row)[WtShape<STEPS>::kLoads], uint32_t have,
+                                        const uint16_t *xrow, bool xreal, int s, int s1, int lane)
+{
+    using W = WtShape<STEPS>;
+    const int g = lane / kTile;
+    const int col = s * 32 + (lane % W::kLanesPerRow) * 8;
+    const bool colok = col < s1 * 32 && col < a.d_model;
+#pragma unroll
+    for (int q = 0; q < W::kLoads; ++q) {
+        bt.w[q] = zero16();
+        bt.w[W::kLoads + q] = zero16();
+        if (((have >> q) & 1u) && colok) {
+            bt.w[q] = load16_stream(a.Wg + (size_t)row[q] * a.d_model + col);
+            bt.w[W::kLoads + q] = load16_stream(a.Wu + (size_t)row[q] * a.d_model + col);
+        }
+    }
+    // a batch inside the row needs no column checks; lanes past the batch read
+    // token 0 there (xrow), which only feeds output columns that are never
+    // stored (MFMA output column j depends on B column j alone)
+    if ((s + STEPS) * 32 <= a.d_model) {  // uniform
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q)
+            bt.x[q] = load16(xrow + (s + q) * 32 + g * 8);
+    } else {
+#pragma unroll
+        for (int q = 0; q < STEPS; ++q) {
+            const int xc = (s + q) * 32 + g * 8;
+            bt.x[q] = load16(or_zero(xreal && xc < a.d_model, xrow + xc));
+        }
+    }
+}
+
+template <int STEPS>
+__device__ __forceinline__ void wt_consume(uint16_t *wt, const WtBatch<STEPS> &bt, int s, int s1,
+                                           int lane, f32x4_t &dg, f32x4_t &du)
+{
+    using W = WtShape<STEPS>;
+    const int i = lane % kTile, g = lane / kTile;
+    const int c = (lane % W::kLanesPerRow) * 8, rr0 = lane / W::kLanesPerRow;
+#pragma unroll
+    for (int q = 0; q < W::kLoads; ++q) {
+        const int rr = W::kRowsPerLoad * q + rr0;
+        *reinterpret_cast<u32x4 *>(wt + rr * W::kStride + c) = bt.w[q];
+        *reinterpret_cast<u32x4 *>(wt + (kTile + rr) * W::kStride + c) = bt.w[W::kLoads + q];
+    }
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q) {
+        if (s + q < s1) {  // uniform
+            const u32x4 ga = *reinterpret_cast<const u32x4 *>(wt + i * W::kStride + q * 32 + g * 8);
+            const u32x4 ua =
+                *reinterpret_cast<const u32x4 *>(wt + (kTile + i) * W::kStride + q * 32 + g * 8);
+            dg = mfma16(ga, bt.x[q], dg);
+            du = mfma16(ua, bt.x[q], du);
+        }
+    }
+}
+
+// The block's active neurons (bits of M, rows r0 + bit) in tiles of 16 on MFMA:
+// each tile's column steps are split among 4 / ntiles waves, which add their
+// 16 x 16 partial sums in `part` (LDS [4][2][256] fp32) and write s = u * SiLU(g).
+// wtiles: LDS [4 waves][WtShape<STEPS>::kWaveElems] bf16; lrow: LDS [32] rows
+// of the active neurons. INTERLEAVE: wave kw of a tile takes batches kw,
+// kw + wpt, ... of STEPS steps, so the tile's waves read adjacent pieces of
+// each row together (after the low-rank score: 57.5 -> 56.7 us per 8B layer at
+// 8 tokens); otherwise each takes one contiguous run of steps (the ternary
+// kernel: interleaved, its layer took 68.2 against 65.4 us). A wave keeps two
+// batches in flight at 4 steps, one at 8.
+template <int B, int NK, bool INTERLEAVE, int STEPS>
+__device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wtiles, float *part,
+                                                int *lrow, uint32_t M, int r0, int wave, int lane)
+{
+    using W = WtShape<STEPS>;
+    constexpr int kWtSteps = STEPS, kWtLoads = W::kLoads;
+    const int n = __builtin_popcount(M);
+    if (threadIdx.x < kPredRows && ((M >> threadIdx.x) & 1u))
+        lrow[__builtin_popcount(M & ((1u << threadIdx.x) - 1u))] = r0 + threadIdx.x;
+    __syncthreads();  // lrow visible; the LDS scratch is free
+
+    const int ntiles = (n + kTile - 1) / kTile;  // 0, 1 or 2
+    if (ntiles == 0)
+        return;
+    const int wpt = kWavesPerBlock / ntiles;
+    const int t0 = (wave / wpt) * kTile, kw = wave % wpt;
+    const int i = lane % kTile, g = lane / kTile;
+    const int steps = (a.d_model + 31) / 32;
+    const int nbat = (steps + kWtSteps - 1) / kWtSteps;  // batches of kWtSteps steps
+    (void)nbat;
+    const bool xreal = i < a.nb;
+    const uint16_t *xrow = a.x + (size_t)(xreal ? i : 0) * a.d_model;
+    int row[kWtLoads];
+    uint32_t have = 0u;
+#pragma unroll
+    for (int q = 0; q < kWtLoads; ++q) {
+        const int k = t0 + W::kRowsPerLoad * q + lane / W::kLanesPerRow;
+        row[q] = k < n ? lrow[k] : r0;
+        have |= (k < n ? 1u : 0u) << q;
+    }
+    uint16_t *wt = wtiles + (size_t)wave * W::kWaveElems;
+    f32x4_t dg = {0.0f, 0.0f, 0.0f, 0.0f}, du = {0.0f, 0.0f, 0.0f, 0.0f};
+    WtBatch<STEPS> b0, b1;  // 4 steps: the next batch is in flight while this one is consumed
+    if constexpr (INTERLEAVE && STEPS >= kWtStepsWide) {
+        for (int j = kw; j < nbat; j += wpt) {
+            wt_load(b0, a, row, have, xrow, xreal, j * kWtSteps, steps, lane);
+            wt_consume(wt, b0, j * kWtSteps, steps, lane, dg, du);
+        }
+    } else if constexpr (INTERLEAVE) {
+        if (kw < nbat)
+            wt_load(b0, a, row, have, xrow, xreal, kw * kWtSteps, steps, lane);
+        for (int j = kw; j < nbat; j += 2 * wpt) {
+            const int jb = j + wpt;
+            if (jb < nbat)
+                wt_load(b1, a, row, have, xrow, xreal, jb * kWtSteps, steps, lane);
+            wt_consume(wt, b0, j * kWtSteps, steps, lane, dg, du);
+            if (jb >= nbat)
+                break;
+            if (jb + wpt < nbat)
+                wt_load(b0, a, row, have, xrow, xreal, (jb + wpt) * kWtSteps, steps, lane);
+            wt_consume(wt, b1, jb * kWtSteps, steps, lane, dg, du);
+        }
+    } else {
+        const int sw = (steps + wpt - 1) / wpt;  // this wave's steps [s0, s1)
+        const int s0 = min(steps, kw * sw), s1 = min(steps, s0 + sw);
+        wt_load(b0, a, row, have, xrow, xreal, s0, s1, lane);
+        for (int s = s0; s < s1; s += 2 * kWtSteps) {
+            const int sb = s + kWtSteps;
+            if (sb < s1)
+                wt_load(b1, a, row, have, xrow, xreal, sb, s1, lane);
+            wt_consume(wt, b0, s, s1, lane, dg, du);
+            if (sb >= s1)
+                break;
+            if (sb + kWtSteps < s1)
+                wt_load(b0, a, row, have, xrow, xreal, sb + kWtSteps, s1, lane);
+            wt_consume(wt, b1, sb, s1, lane, dg, du);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int e = (4 * g + r) * kTile + i;  // D[4g + r][i]
+        part[(wave * 2 + 0) * 256 + e] = dg[r];
+        part[(wave * 2 + 1) * 256 + e] = du[r];
+    }
+    __syncthreads();
+    const int ti = threadIdx.x / kTile, tj = threadIdx.x % kTile;  // D[ti][tj] of each tile
+    for (int tile = 0; tile < ntiles; ++tile) {
+        float gs = 0.0f, us = 0.0f;
+        for (int v = tile * wpt; v < (tile + 1) * wpt; ++v) {
+            gs += part[(v * 2 + 0) * 256 + threadIdx.x];
+            us += part[(v * 2 + 1) * 256 + threadIdx.x];
+        }
+        const int rank = tile * kTile + ti;
+        if (rank < n && tj < a.nb)
+            a.s[(size_t)tj * a.d_ff + lrow[rank]] = us * silu(gs);
+    }
+}
+
+// Practical D-CountDown coefficient kernel for batches of 4-8 (Sec. 4): the
+// scoring of k_coef_pred, then the block's active neurons in tiles of 16 on MFMA.
+template <int B, int NK, int LCPR>
+__global__ __launch_bounds__(kBlock) void k_coef_pred_mfma(const CoefArgs a)
+{
+    // LDS: the waves' weight tiles [4][kWaveElems] bf16, then the latent [B][d_rank]
+    // fp32 (rank 1024 only), whose space later holds the partial sums [4][2][16 x 16]
+    extern __shared__ __align__(16) uint32_t xs[];
+    __shared__ uint32_t wflag[kWavesPerBlock];
+    __shared__ int lrow[kPredRows];
+    using S = PredShape<LCPR>;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int r0 = blockIdx.x * kPredRows;
+    const int wr0 = r0 + wave * kPredRowsPerWave;
+
+    using LR = LatentRegs<B, LCPR>;
+    u32x4 wb[S::kLoads];
+    pred_issue_bt<LCPR>(wb, a, wr0, lane);
+    LR lr;
+    lr.issue(a.lat, a.nb, a.d_rank, lane);
+    LatentStage<LR::kRegs ? 1 : B> ls;  // the LDS copy, rank 1024 only
+    if constexpr (!LR::kRegs)
+        ls.issue(a.lat, a.nb, a.d_rank);
+    __builtin_amdgcn_sched_barrier(0);
+    zero_y(a.y, a.nb * a.d_model);
+    uint16_t *wtiles = reinterpret_cast<uint16_t *>(xs);
+    constexpr int STEPS = LR::kRegs ? kWtStepsWide : kWtStepsNarrow;
+    uint32_t *latw = xs + kWavesPerBlock * WtShape<STEPS>::kWaveElems / 2;
+    if constexpr (!LR::kRegs) {
+        ls.write(reinterpret_cast<u32x4 *>(latw), a.lat, a.nb, a.d_rank);
+        __syncthreads();
+    }
+
+    const uint32_t wmask = pred_score<B, LCPR>(wb, lr, reinterpret_cast<const float *>(latw), a,
+                                               wr0, lane);
+    if (lane == 0)
+        wflag[wave] = wmask;
+    __syncthreads();
+    uint32_t M = 0;
+#pragma unroll
+    for (int v = 0; v < kWavesPerBlock; ++v)
+        M |= wflag[v] << (v * kPredRowsPerWave);
+    // the latent is no longer read once gather_mfma_lds's first barrier has passed
+    gather_mfma_lds<B, NK, true, STEPS>(a, wtiles, reinterpret_cast<float *>(latw), lrow, M, r0,
+                                        wave, lane);
+}
+
 // ------------------------------------------------ ternary predictor
 // The TernaryLinear predictor of the paper's appendix: s_hat = x . theta with
 // theta in {-1, 0, +1}^{d_model x d_ff}, thresholded like the low-rank score
@@ -2154,7 +2401,7 @@ int tern_row_words(int d_model)
 // and the LDS copy measured 8-20% faster there (70B shape: ideal D, low-rank and
 // ternary predictors, dense); at one token, and two of d_model <= 4096, the
 // registers are as fast or faster.
-constexpr bool tokens_in_regs(int bt, int nk) { return bt == 1 || nk <= 8; }
+constexpr bool tokens_in_regs(int bt, int nk) { return bt == 1 || (bt == 2 && nk <= 8); }
 
 static size_t token_lds_bytes(int bt, int nk)
 {
@@ -2203,6 +2450,15 @@ static void coef_pred_lcpr(const CoefArgs &a, hipStream_t s)
 {
     const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
     const size_t lat_lds = LatentRegs<B, LCPR>::kRegs ? 0 : (size_t)B * a.d_rank * 4;
+    if constexpr (B >= 8) {
+        // weight tiles, then max(latent, 4 x 2 x 16 x 16 partial sums)
+        constexpr int STEPS = LatentRegs<B, LCPR>::kRegs ? kWtStepsWide : kWtStepsNarrow;
+        const size_t lds = (size_t)kWavesPerBlock * WtShape<STEPS>::kWaveElems * 2 +
+                           max(lat_lds, (size_t)kWavesPerBlock * 2 * 256 * 4);
+        allow_lds(k_coef_pred_mfma<B, NK, LCPR>, lds);
+        k_coef_pred_mfma<B, NK, LCPR><<<grid, kBlock, lds, s>>>(a);
+        return;
+    }
     constexpr bool XR = pred_tokens_in_regs(B, NK);
     const size_t lds = (XR ? 0 : (size_t)B * NK * kColsPerLoad * 2) + lat_lds;
     allow_lds(k_coef_pred<B, NK, XR, LCPR, pred_waves(NK)>, lds);
@@ -2267,9 +2523,12 @@ static hipError_t coef_bn(int variant, const CoefArgs &a, hipStream_t s)
         k_coef_dual<B, NK, XREG, false><<<grid, kBlock, lds, s>>>(a);
         break;
     case kDense:
-        allow_lds(k_coef_dual<B, NK, XREG, true>, lds);
-        k_coef_dual<B, NK, XREG, true><<<grid, kBlock, lds, s>>>(a);
-        break;
+        if constexpr (B <= 2) {  // (from 3 tokens: launch_batch)
+            allow_lds(k_coef_dual<B, NK, XREG, true>, lds);
+            k_coef_dual<B, NK, XREG, true><<<grid, kBlock, lds, s>>>(a);
+            break;
+        }
+        return hipErrorInvalidValue;
     case kDualPred:
         return coef_pred_launch<B, NK>(a, s);
     case kDualTern:
@@ -2291,15 +2550,28 @@ static hipError_t coef_b(int variant, const CoefArgs &a, hipStream_t s)
     case 4: return coef_bn<B, 4>(variant, a, s);
     case 8: return coef_bn<B, 8>(variant, a, s);
     default:
-        return coef_bn<B, 16>(variant, a, s);
+        // batch * d_model is capped at 32768 by the plan checks: no 8 x 8192 tile
+        if constexpr (B * 16 <= 64)
+            return coef_bn<B, 16>(variant, a, s);
+        return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_coef(int variant, const CoefArgs &a, hipStream_t s)
+// stacked: a layer of a residual stack, where x is rounded to bf16 between the layers. A
+// last-bit difference in a coefficient reaches the next layers through that rounding and
+// their thresholds (one neuron more or less moves y by 1-4%), so the thresholded variants
+// keep the kernels whose sums earlier results of a stack came from; the MFMA kernels of
+// cd_batch.hpp add in another order. Single layers, and the dense stack, take the latter.
+hipError_t launch_coef(int variant, const CoefArgs &a, bool stacked, hipStream_t s)
 {
-    if (batch_kernels(variant, a.nb))
+    if (batch_kernels(variant, a.nb) && (!stacked || variant == kDense))
         return launch_batch(variant, a, nullptr, s);
-    return a.nb == 1 ? coef_b<1>(variant, a, s) : coef_b<2>(variant, a, s);
+    switch (batch_tile(a.nb)) {
+    case 1: return coef_b<1>(variant, a, s);
+    case 2: return coef_b<2>(variant, a, s);
+    case 4: return coef_b<4>(variant, a, s);
+    default: return coef_b<8>(variant, a, s);
+    }
 }
 
 template <int B>
