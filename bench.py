@@ -31,7 +31,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E peak, GB/s
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2505_17701_amd", "csrc", f)
-               for f in ("cd_kernels.hip", "cd_device.hpp", "cd_internal.hpp")]
+               for f in ("cd_kernels.hip", "cd_batch.hpp", "cd_calib.hpp", "cd_device.hpp",
+                         "cd_internal.hpp")]
 # committed FETCH_SIZE / WRITE_SIZE summaries of a line's dominant kernel(s), by
 # (workload, variant, k, batch)
 TRAFFIC_SUMMARIES = {
@@ -40,13 +41,13 @@ TRAFFIC_SUMMARIES = {
     ("llama3_8b_4096x14336_pred", "dual_pred", 0.9, 1):
         "k_coef_pred_llama3_8b_4096x14336_k0.9_b1_traffic.md",
     ("llama3_8b_4096x14336_pred", "dual_pred", 0.9, 4):
-        "k_coef_pred_llama3_8b_4096x14336_k0.9_b4_traffic.md",
+        "k_batch_pred_llama3_8b_4096x14336_k0.9_b4_traffic.md",
     ("llama3_8b_4096x14336_pred", "dual_pred", 0.9, 8):
-        "k_coef_pred_mfma_llama3_8b_4096x14336_k0.9_b8_traffic.md",
+        "k_batch_pred_llama3_8b_4096x14336_k0.9_b8_traffic.md",
     ("llama3_8b_4096x14336_pred", "dual_tern", 0.9, 1):
         "k_coef_tern_llama3_8b_4096x14336_k0.9_b1_traffic.md",
     ("llama3_8b_4096x14336_pred", "dual_tern", 0.9, 8):
-        "k_coef_tern_mfma_llama3_8b_4096x14336_k0.9_b8_traffic.md",
+        "k_batch_tern_llama3_8b_4096x14336_k0.9_b8_traffic.md",
 }
 
 
@@ -449,26 +450,28 @@ def optimal_dense_us(ctx, k, steps):
 
 def kernel_desc(variant, B=1):
     """The kernel(s) of a line's coefficient phase, the dominant part of every call."""
-    pred = ("k_coef_pred_mfma" if B >= 5 else
-            "k_coef_pred (8 waves per block)" if B >= 3 else "k_coef_pred")
-    tern = ("k_coef_tern_mfma (score on MFMA at d_model 4096)" if B >= 5 else
-            "k_coef_tern (8 waves per block)" if B >= 3 else "k_coef_tern")
-    sel = "k_topk_gather1 (select, flags and gather in one launch)" if B == 1 else \
-        "k_topk_select + k_gather_topk"
-    return {"mono": "k_coef_mono (dense W_up GEMV, threshold, wave-local W_gate gather, s)",
-            "dual_ideal": "k_coef_dual (dense W_gate + W_up GEMV, s, threshold)",
+    batched = B >= 3  # the MFMA kernels of 3-8 tokens (the ternary predictor: from 2)
+    mono = "k_batch_mono" if batched else "k_coef_mono"
+    dual = "k_batch_dual" if batched else "k_coef_dual"
+    pred = "k_batch_pred" if batched else "k_coef_pred"
+    tern = "k_batch_tern" if B >= 2 else "k_coef_tern"
+    cats = mono if batched else "k_coef_mono<CATS>"
+    sel = ("k_topk_gather1 (select, flags and gather in one launch)" if B == 1 else
+           "k_topk_select + " + ("k_batch_topk" if batched else "k_gather_topk_w"))
+    return {"mono": f"{mono} (dense W_up GEMV, threshold, W_gate gather, s)",
+            "dual_ideal": f"{dual} (dense W_gate + W_up GEMV, s, threshold)",
             "dual_pred": f"k_latent + {pred} (predictor latent, scores, threshold, block-local "
                          "W_gate / W_up gather, s)",
-            "dense": "k_coef_dual (dense W_gate + W_up GEMV, s)",
-            "mono_topk": f"k_coef_mono + {sel} (per-token threshold)",
-            "dual_ideal_topk": "k_coef_dual + k_topk_select (per-token threshold; the select "
+            "dense": f"{dual} (dense W_gate + W_up GEMV, s)",
+            "mono_topk": f"{mono} + {sel} (per-token threshold)",
+            "dual_ideal_topk": f"{dual} + k_topk_select (per-token threshold; the select "
                                "sets the flags, s is the coefficient)"
                                + ("; the phase timed alone: a whole one-token call runs "
                                   "k_coef_dual, then k_topk_down1 (select, flags and down "
                                   "projection in one launch)" if B == 1 else ""),
             "dual_pred_topk": f"k_latent + {pred} + {sel} (per-token threshold)",
-            "cats": "k_coef_mono<CATS> (dense W_gate GEMV, SiLU, threshold, W_up gather)",
-            "cats_topk": f"k_coef_mono<CATS> + {sel} (per-token threshold)",
+            "cats": f"{cats} (dense W_gate GEMV, SiLU, threshold, W_up gather)",
+            "cats_topk": f"{cats} + {sel} (per-token threshold)",
             "dual_tern": f"{tern} (ternary predictor scores, threshold, block-local W_gate / "
                          "W_up gather, s)",
             "dual_tern_topk": f"{tern} + {sel} (per-token threshold)"

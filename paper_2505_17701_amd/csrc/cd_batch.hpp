@@ -213,7 +213,7 @@ __device__ __forceinline__ void run_quads(const BufRsrc (&m)[NM], int nq, RowF r
                                           TokenSlice<TQ, S, TERN> &tok, PartSums<TQ> sums,
                                           int wave, int lane)
 {
-        constexpr int D = S >= 6 ? 1 : 2;  // items in flight
+    constexpr int D = S >= 6 ? 1 : 2;  // items in flight
     u32x4 buf[D][S];
     const int n = nq * NM;
     const auto issue = [&](u32x4 (&w)[S], int it) {
