@@ -454,7 +454,7 @@ def kernel_desc(variant, B=1):
     mono = "k_batch_mono" if batched else "k_coef_mono"
     dual = "k_batch_dual" if batched else "k_coef_dual"
     pred = "k_batch_pred" if batched else "k_coef_pred"
-    tern = "k_batch_tern" if B >= 2 else "k_coef_tern"
+    tern = "k_batch_tern" if B >= 2 else "k_coef_tern"  # (2 tokens: up to d_model 4096)
     cats = mono if batched else "k_coef_mono<CATS>"
     sel = ("k_topk_gather1 (select, flags and gather in one launch)" if B == 1 else
            "k_topk_select + " + ("k_batch_topk" if batched else "k_gather_topk_w"))

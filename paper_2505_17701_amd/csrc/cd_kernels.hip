@@ -518,13 +518,21 @@ template <int B, int NK, bool XREG, int NW>
 __device__ __forceinline__ void gather_rr(const CoefArgs &a, const Tokens<B, NK, XREG> &tok,
                                           uint32_t m, int r0, int lane)
 {
+    // (the loads before the loop: as one loop around loads and sums the low-rank kernel at
+    // 1 token of 7000 x 14000, k 0.5, took 69.7 us against 63.6)
     int r = pred_next<NW>(m);
-    while (r >= 0) {
-        u32x4 g[NK], u[NK];
-        load_row<NK>(g, a.Wg + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
-        load_row<NK>(u, a.Wu + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
+    if (r < 0)
+        return;
+    u32x4 g[NK], u[NK];
+    load_row<NK>(g, a.Wg + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
+    load_row<NK>(u, a.Wu + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
+    for (;;) {
         pred_finish<B, NK, XREG>(a, tok, g, u, r0 + r, lane);
         r = pred_next<NW>(m);
+        if (r < 0)
+            break;
+        load_row<NK>(g, a.Wg + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
+        load_row<NK>(u, a.Wu + (size_t)(r0 + r) * a.d_model, a.d_model, lane);
     }
 }
 
@@ -2362,12 +2370,13 @@ namespace cdk {
 // Batches from which the MFMA kernels of cd_batch.hpp run. At 2 tokens half of their
 // products are of empty token columns, and only the ternary predictor gains, whose
 // scores move from v_dot2 to MFMA (4096 x 14336: 29.0 -> 26.2 us; M at 4096 x 11008 28.8
-// against 32.8, dense 49.1 against 49.9, low-rank predictor 28.0 against 29.3).
+// against 32.8, dense 49.1 against 49.9, low-rank predictor 28.0 against 29.3), up to 4096
+// columns (7000 x 14000 at k 0.5: 111.6 us on MFMA, 95.9 in k_coef_tern).
 constexpr int kBatchMin = 3;
 
-static bool batch_kernels(int variant, int nb)
+static bool batch_kernels(int variant, int nb, int d_model)
 {
-    return nb >= kBatchMin || (nb == 2 && variant == kDualTern);
+    return nb >= kBatchMin || (nb == 2 && variant == kDualTern && d_model <= 4096);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -2532,7 +2541,7 @@ static hipError_t coef_bn(int variant, const CoefArgs &a, hipStream_t s)
     case kDualPred:
         return coef_pred_launch<B, NK>(a, s);
     case kDualTern:
-        if constexpr (B == 1)  // (from 2 tokens: launch_batch)
+        if constexpr (B == 1 || (B == 2 && NK > 8))  // (else launch_batch)
             return coef_tern_launch<B, NK>(a, s);
         return hipErrorInvalidValue;
     default:
@@ -2564,7 +2573,7 @@ static hipError_t coef_b(int variant, const CoefArgs &a, hipStream_t s)
 // cd_batch.hpp add in another order. Single layers, and the dense stack, take the latter.
 hipError_t launch_coef(int variant, const CoefArgs &a, bool stacked, hipStream_t s)
 {
-    if (batch_kernels(variant, a.nb) && (!stacked || variant == kDense))
+    if (batch_kernels(variant, a.nb, a.d_model) && (!stacked || variant == kDense))
         return launch_batch(variant, a, nullptr, s);
     switch (batch_tile(a.nb)) {
     case 1: return coef_b<1>(variant, a, s);
