@@ -399,6 +399,9 @@ cd_status dalloc(T **ptr, size_t count)
     if (e == hipSuccess)
         return CD_OK;
     *ptr = nullptr;
+    // This call reports the failure; HIP would keep it for the hipGetLastError of the next
+    // launch on this thread (later successes do not clear it).
+    (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? CD_ENOMEM : CD_EHIP;
 }
 
