@@ -642,13 +642,19 @@ __global__ __launch_bounds__(kBatThreads, 4) void k_batch_topk(const CoefArgs a,
 // rate and not much more, so what one has too much is not made up elsewhere. (Blocks of
 // 32 neurons, 344 workgroups, left two thirds of the CUs idle for half of the dense 4096 x
 // 11008 layer: 62 us against 52 at 4 tokens; three workgroups per CU reload the tokens
-// and measured 2-5 us slower.) Layers of less than two quads per workgroup take one
-// quad each, in a multiple of kCus or fewer than kCus workgroups.
-inline int batch_grid(int d_ff)
+// and measured 2-5 us slower.)
+// One per CU up to three quads per CU, where a workgroup's barriers and token loads weigh
+// more than its rows: 4096 x 2048, M at 8 tokens 18.1 us with two, 16.2 with one, low-rank
+// (rank 128) 22.7 against 20.8; from 4096 neurons on two are even or faster (1024 x 8192
+// ternary at 8 tokens 9% faster). And one per CU up to eight quads, a workgroup's most,
+// where each workgroup keeps the latents in LDS (rank 1024): 1024 x 4096 at 8 tokens 57.3 us
+// with two, 39.7 with one; 4096 x 8192 69.8 against 56.8.
+inline int batch_grid(int d_ff, bool lds_latent)
 {
     const int quads = d_ff / 4, per = 2 * kCus * kQuads;
-    const int g = (quads + per - 1) / per * 2 * kCus;
-    return g <= quads ? g : quads < kCus ? quads : kCus;
+    if (quads <= (lds_latent ? kQuads : 3) * kCus)
+        return quads < kCus ? quads : kCus;
+    return (quads + per - 1) / per * 2 * kCus;
 }
 
 // steps of 128 columns per wave
@@ -676,7 +682,7 @@ static hipError_t batch_pred(const CoefArgs &a, int grid, hipStream_t s)
 template <int TQ, int S>
 static hipError_t batch_ts(int variant, const CoefArgs &a, const double *q, hipStream_t s)
 {
-    const int grid = batch_grid(a.d_ff);
+    const int grid = batch_grid(a.d_ff, variant == kDualPred && !q && a.d_rank == 1024);
     if (q) {
         if (variant == kDualPred)
             k_batch_topk<2, TQ, S><<<grid, kBatThreads, 0, s>>>(a, q, false);
@@ -698,7 +704,7 @@ static hipError_t batch_ts(int variant, const CoefArgs &a, const double *q, hipS
 template <int TQ>
 static hipError_t batch_tern(const CoefArgs &a, hipStream_t s)
 {
-    const int grid = batch_grid(a.d_ff);
+    const int grid = batch_grid(a.d_ff, false);
     const int words = tern_row_words(a.d_model);
     switch (col_tile(a.d_model)) {  // units of 512 columns: two per wave step
     case 1:

@@ -37,6 +37,9 @@ CASES = [
     # 1-2, of 8, and the first size with two generations
     ("mono", 64, 1016, 3, 0), ("mono", 64, 1032, 8, 0), ("dual_pred", 64, 2056, 4, 16),
     ("dual_ideal", 64, 2048, 3, 0), ("mono", 64, 16384, 5, 0), ("dual_tern", 64, 16392, 4, 0),
+    # one workgroup per CU up to three quads each, or eight with the latent in LDS; two past it
+    ("mono", 64, 3072, 5, 0), ("mono", 64, 3080, 8, 0), ("dual_pred", 64, 8192, 4, 1024),
+    ("dual_pred", 64, 8200, 8, 1024),
 ]
 
 

@@ -1,0 +1,41 @@
+"""Which kernels a call launches, and with how many workgroups, at the edges of the dispatch
+rules: read off the library's host code, without a GPU."""
+import pytest
+
+import host_hip
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    return host_hip.Host(host_hip.build(str(tmp_path_factory.mktemp("host"))))
+
+
+def ffn_launches(host, variant, d_model, d_ff, B, rank=0, thld=1.0):
+    st, h = host.plan(d_model, d_ff, B, rank)
+    assert st == host.cd.CD_OK
+    host.launches()
+    assert host.ffn(h, variant, B, thld) == host.cd.CD_OK
+    out = host.launches()
+    host.lib.countdown_plan_destroy(h)
+    return out
+
+
+@pytest.mark.parametrize("variant,d_model,d_ff,B,rank,grid", [
+    ("mono", 4096, 8, 3, 0, 2), ("mono", 4096, 1016, 3, 0, 254), ("dense", 4096, 1032, 8, 0, 256),
+    # one workgroup per CU up to three quads of neurons, two past that, then whole multiples
+    ("mono", 4096, 2048, 8, 0, 256), ("dual_ideal", 4096, 3072, 4, 0, 256),
+    ("mono", 4096, 3080, 8, 0, 512), ("dual_pred", 4096, 3080, 8, 512, 512),
+    ("dual_tern", 4096, 16384, 3, 0, 512), ("dual_pred", 4096, 16392, 8, 64, 1024),
+    # the latents of rank 1024 lie in LDS: one workgroup per CU as far as it reaches
+    ("dual_pred", 4096, 2048, 8, 1024, 256), ("dual_pred", 1024, 8192, 4, 1024, 256),
+    ("dual_pred", 1024, 8200, 8, 1024, 512),
+])
+def test_batch_grid(host, variant, d_model, d_ff, B, rank, grid):
+    got = [n for k, n in ffn_launches(host, variant, d_model, d_ff, B, rank)
+           if k.startswith("k_batch_")]
+    assert got == [grid]
+    assert grid <= d_ff // 4  # a quad of neurons per workgroup at least
+    shares = min(grid, 256)   # and eight at most, as k_batch_* spread them
+    for share in range(shares):
+        lo, hi = d_ff // 4 * share // shares, d_ff // 4 * (share + 1) // shares
+        assert -(-(hi - lo) // (grid // shares)) <= 8
