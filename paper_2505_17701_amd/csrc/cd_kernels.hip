@@ -9,8 +9,8 @@
 //     the two-row kernel; otherwise an LDS copy per workgroup) with
 //     v_dot2_f32_bf16, reduces across the wave with DPP and applies the
 //     strict threshold (union over the batch). Batches of 3-8 run the MFMA
-//     kernels of cd_batch.hpp instead. For M-CountDown an active
-//     neuron's wave immediately reads its W_gate row and forms s = u *
+//     kernels of cd_batch.hpp instead, but for small layers (batch_coef) and
+//     residual stacks (launch_coef). For M-CountDown an active neuron's wave immediately reads its W_gate row and forms s = u *
 //     SiLU(g). Results land in per-neuron arrays act[d_ff] and s[B][d_ff];
 //     there are no barriers between waves. The kernel also zeroes y.
 //   predictor (practical D-CountDown): the latent x . theta_A (one workgroup
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_pred(const CoefArgs a)
     gather_rr<B, NK, XREG, NWV>(a, tok, m, r0, lane);
 }
 
-// ----------------- MFMA gather for 5-8 tokens of a residual stack (see launch_coef)
+// ----------- MFMA gather for 5-8 tokens of narrow layers and residual stacks (batch_coef)
 // For 5-8 tokens the gathered products are small dense contractions: a tile
 // of 16 active neurons times the batch, on v_mfma_f32_16x16x32_bf16. Lane
 // l = i + 16 g (i = l % 16, g = l / 16) supplies row i of the tile (A operand)
@@ -791,7 +791,7 @@ __device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wti
     }
 }
 
-// Practical D-CountDown coefficient kernel for batches of 4-8 (Sec. 4): the
+// Practical D-CountDown coefficient kernel for batches of 5-8 (Sec. 4): the
 // scoring of k_coef_pred, then the block's active neurons in tiles of 16 on MFMA.
 template <int B, int NK, int LCPR>
 __global__ __launch_bounds__(kBlock) void k_coef_pred_mfma(const CoefArgs a)
@@ -962,8 +962,8 @@ __device__ __forceinline__ uint32_t tern_score(const TernRows<NK> &t, XF xget, c
     return wmask;
 }
 
-// Ternary-predictor coefficient kernel for one token: k_coef_pred with
-// the ternary score in place of the latent . B_t one (no latent kernel).
+// Ternary-predictor coefficient kernel for one token, and for two past 4096 columns:
+// k_coef_pred with the ternary score in place of the latent . B_t one (no latent kernel).
 template <int B, int NK, bool XREG, int NWV>
 __global__ __launch_bounds__(NWV * kWave) void k_coef_tern(const CoefArgs a)
 {
@@ -2374,9 +2374,30 @@ namespace cdk {
 // columns (7000 x 14000 at k 0.5: 111.6 us on MFMA, 95.9 in k_coef_tern).
 constexpr int kBatchMin = 3;
 
-static bool batch_kernels(int variant, int nb, int d_model)
+// Whether the coefficients of a call come from the MFMA kernels. From 3 tokens on they do,
+// but for small layers: a workgroup's waves share its rows by columns, a step of 128 each,
+// so up to 1024 columns a wave has one step per four neurons and what counts is the chain of
+// barriers and LDS sums after it. Measured (MFMA against the kernel of 1-2 tokens with a
+// token tile of 4 or 8):
+//  - 3-4 tokens, few neurons: M 512 x 3000 10.5 against 9.4 us, 512 x 7000 12.3 against 11.5,
+//    1024 x 4096 11.4 against 10.9, 2048 x 3000 12.1 against 11.9; dense 512 x 4096 11.6
+//    against 11.2. Past the lines it turns: M 512 x 11008 14.3 and 14.3, 2048 x 5632 15.3
+//    against 15.6; ideal 1032 x 3000 11.3 against 11.8, dense 512 x 11008 17.7 against 18.1.
+//    Two rows a neuron count twice.
+//  - the low-rank predictor at 5-8 tokens of one 512-column chunk, where the 16 x 16 tiles of
+//    k_coef_pred_mfma need one pass: rank 128, 512 x 11008 22.6 against 21.3 us, rank 16, 256
+//    x 28672 29.4 against 24.3; up to 3072 neurons (2504: 16.3 against 16.5), past 512
+//    columns (520 x 11008: 23.3 against 24.0) and past rank 256 (512: 27.2 against 28.3) not.
+static bool batch_coef(int variant, const CoefArgs &a)
 {
-    return nb >= kBatchMin || (nb == 2 && variant == kDualTern && d_model <= 4096);
+    if (variant == kDualTern)
+        return a.nb >= kBatchMin || (a.nb == 2 && a.d_model <= 4096);
+    if (a.nb < kBatchMin)
+        return false;
+    if (variant == kDualPred)
+        return !(a.nb > 4 && a.d_model <= 512 && a.d_ff > 3072 && a.d_rank <= 256);
+    const int cols = a.d_model * (variant == kMono || variant == kCats ? 1 : 2);
+    return !(a.nb <= 4 && a.d_ff <= (cols <= 1024 ? 7168 : cols <= 2048 ? 3072 : 0));
 }
 
 // ------------------------------------------------------------------ launchers
@@ -2532,7 +2553,7 @@ static hipError_t coef_bn(int variant, const CoefArgs &a, hipStream_t s)
         k_coef_dual<B, NK, XREG, false><<<grid, kBlock, lds, s>>>(a);
         break;
     case kDense:
-        if constexpr (B <= 2) {  // (from 3 tokens: launch_batch)
+        if constexpr (B <= 2 || (B == 4 && NK <= 2)) {  // (else launch_batch)
             allow_lds(k_coef_dual<B, NK, XREG, true>, lds);
             k_coef_dual<B, NK, XREG, true><<<grid, kBlock, lds, s>>>(a);
             break;
@@ -2573,7 +2594,7 @@ static hipError_t coef_b(int variant, const CoefArgs &a, hipStream_t s)
 // cd_batch.hpp add in another order. Single layers, and the dense stack, take the latter.
 hipError_t launch_coef(int variant, const CoefArgs &a, bool stacked, hipStream_t s)
 {
-    if (batch_kernels(variant, a.nb, a.d_model) && (!stacked || variant == kDense))
+    if (batch_coef(variant, a) && (!stacked || variant == kDense))
         return launch_batch(variant, a, nullptr, s);
     switch (batch_tile(a.nb)) {
     case 1: return coef_b<1>(variant, a, s);

@@ -40,6 +40,12 @@ CASES = [
     # one workgroup per CU up to three quads each, or eight with the latent in LDS; two past it
     ("mono", 64, 3072, 5, 0), ("mono", 64, 3080, 8, 0), ("dual_pred", 64, 8192, 4, 1024),
     ("dual_pred", 64, 8200, 8, 1024),
+    # the kernels of 1-2 tokens with a tile of 4 or 8 on one side of the lines of small layers,
+    # the batch kernels (one or two steps a wave at 3-4 tokens) on the other
+    ("mono", 1024, 7168, 3, 0), ("mono", 1024, 7176, 4, 0), ("cats", 8, 7176, 3, 0),
+    ("cats", 2048, 3072, 4, 0), ("mono", 2048, 3080, 3, 0), ("dual_ideal", 512, 7168, 4, 0),
+    ("dual_ideal", 512, 7176, 3, 0), ("dual_ideal", 1024, 3080, 4, 0), ("mono", 2056, 40, 4, 0),
+    ("dual_pred", 512, 3080, 8, 256), ("dual_pred", 520, 3080, 5, 8), ("dual_pred", 8, 3080, 5, 16),
 ]
 
 

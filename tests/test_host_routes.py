@@ -39,3 +39,30 @@ def test_batch_grid(host, variant, d_model, d_ff, B, rank, grid):
     for share in range(shares):
         lo, hi = d_ff // 4 * share // shares, d_ff // 4 * (share + 1) // shares
         assert -(-(hi - lo) // (grid // shares)) <= 8
+
+
+MFMA, ROWS = "batch", "rows"
+
+
+@pytest.mark.parametrize("variant,d_model,d_ff,B,rank,kind", [
+    # few neurons at 3-4 tokens: one row a neuron up to 1024 / 2048 columns, two rows half that
+    ("mono", 8, 7168, 3, 0, ROWS), ("mono", 1024, 7168, 4, 0, ROWS), ("mono", 1024, 7176, 3, 0, MFMA),
+    ("cats", 1032, 3072, 4, 0, ROWS), ("cats", 2048, 3080, 4, 0, MFMA), ("mono", 2056, 8, 3, 0, MFMA),
+    ("mono", 512, 3072, 5, 0, MFMA), ("cats", 8, 8, 8, 0, MFMA),
+    ("dense", 512, 7168, 4, 0, ROWS), ("dense", 520, 7168, 3, 0, MFMA), ("dense", 1024, 3072, 4, 0, ROWS),
+    ("dense", 1032, 8, 4, 0, MFMA), ("dual_ideal", 1024, 3080, 3, 0, MFMA),
+    ("dual_ideal", 512, 7168, 3, 0, ROWS), ("dense", 512, 688, 5, 0, MFMA),
+    # one chunk of columns, many neurons, a short rank at 5-8 tokens
+    ("dual_pred", 512, 3080, 5, 256, ROWS), ("dual_pred", 512, 3072, 8, 64, MFMA),
+    ("dual_pred", 520, 28672, 8, 64, MFMA), ("dual_pred", 512, 28672, 8, 512, MFMA),
+    ("dual_pred", 512, 28672, 4, 64, MFMA), ("dual_pred", 8, 28672, 8, 8, ROWS),
+    # the ternary predictor: 2 tokens up to 4096 columns, 3 and more always
+    ("dual_tern", 4096, 688, 2, 0, MFMA), ("dual_tern", 4104, 688, 2, 0, ROWS),
+    ("dual_tern", 64, 688, 3, 0, MFMA), ("dual_tern", 64, 688, 1, 0, ROWS),
+    ("mono", 4096, 14336, 2, 0, ROWS),
+])
+def test_coefficient_kernel(host, variant, d_model, d_ff, B, rank, kind):
+    coef = [k for k, _ in ffn_launches(host, variant, d_model, d_ff, B, rank)
+            if k.startswith(("k_batch_", "k_coef_"))]
+    assert len(coef) == 1
+    assert coef[0].startswith("k_batch_" if kind == MFMA else "k_coef_"), coef
