@@ -591,6 +591,37 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_pred(const CoefArgs a)
     gather_rr<B, NK, XREG, NWV>(a, tok, m, r0, lane);
 }
 
+// The scores of k_coef_pred alone, for a threshold of +inf, above which no score lies: the
+// first pass of the per-token thresholds and of a small calibration. Nothing is gathered, so
+// the tokens are not loaded, and four waves a block are enough: with k_coef_pred's eight and
+// its token copy in LDS a per-token call at 1 token of 1024 x 3000, rank 512, took 18.6 us
+// (18.0 with four waves and the tokens in registers); here 17.8.
+template <int B, int LCPR>
+__global__ __launch_bounds__(kBlock) void k_score_pred(const CoefArgs a)
+{
+    extern __shared__ __align__(16) uint32_t xs[];  // latent [B][d_rank] (rank 1024 only)
+    using LR = LatentRegs<B, LCPR>;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int wr0 = blockIdx.x * kPredRows + wave * kPredRowsPerWave;
+    u32x4 wb[PredShape<LCPR>::kLoads];
+    pred_issue_bt<LCPR>(wb, a, wr0, lane);
+    LR lr;
+    lr.issue(a.lat, a.nb, a.d_rank, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!LR::kRegs) {
+        LatentStage<B> ls;
+        ls.issue(a.lat, a.nb, a.d_rank);
+        ls.write(reinterpret_cast<u32x4 *>(xs), a.lat, a.nb, a.d_rank);
+        __syncthreads();
+    }
+    // Every load here before the first score is stored (vmcnt 0): loads and stores share a
+    // counter, so a later row's wait would take in the stores of the rows before it. y last,
+    // for the same reason.
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    (void)pred_score<B, LCPR>(wb, lr, reinterpret_cast<const float *>(xs), a, wr0, lane);
+    zero_y(a.y, a.nb * a.d_model);
+}
+
 // ----------- MFMA gather for 5-8 tokens of narrow layers and residual stacks (batch_coef)
 // For 5-8 tokens the gathered products are small dense contractions: a tile
 // of 16 active neurons times the batch, on v_mfma_f32_16x16x32_bf16. Lane
@@ -1005,6 +1036,22 @@ __global__ __launch_bounds__(NWV * kWave) void k_coef_tern(const CoefArgs a)
     }
     const uint32_t m = block_share(wflag, wmask, wave, lane);
     gather_rr<B, NK, XREG, NWV>(a, tok, m, r0, lane);
+}
+
+// The scores of k_coef_tern alone (a threshold of +inf, as k_score_pred), one token in
+// registers: a per-token call of 4096 x 3000 took 19.8 us with k_coef_tern's eight waves (19.3
+// with four and the token in registers), here 18.8.
+template <int NK>
+__global__ __launch_bounds__(kBlock) void k_score_tern(const CoefArgs a)
+{
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int wr0 = blockIdx.x * kPredRows + wave * kPredRowsPerWave;
+    TernRows<NK> tr;
+    tr.issue(a, wr0, lane);
+    Tokens<1, NK, true> tok;
+    tok.issue(a.x, a.nb, a.d_model, lane);
+    zero_y(a.y, a.d_model);
+    (void)tern_score<1, NK, false>(tr, [&](int b, int j) { return tok.r[b][j]; }, a, wr0, lane);
 }
 
 // latent = x . theta_A for the predictor: one workgroup per row of A_t, the
@@ -2475,6 +2522,9 @@ void down_grid(int d_model, int d_ff, int bt, int *gc, int *gr, int *rows_per_gr
 constexpr int pred_waves(int nk) { return nk <= 8 ? 8 : kWavesPerBlock; }
 constexpr bool pred_tokens_in_regs(int bt, int nk) { return nk > 8 && tokens_in_regs(bt, nk); }
 
+// no score passes a threshold of +inf (the predictors' selection is strict)
+static bool scores_only(const CoefArgs &a) { return a.thld == INFINITY; }
+
 template <int B, int NK, int LCPR>
 static void coef_pred_lcpr(const CoefArgs &a, hipStream_t s)
 {
@@ -2488,6 +2538,12 @@ static void coef_pred_lcpr(const CoefArgs &a, hipStream_t s)
         allow_lds(k_coef_pred_mfma<B, NK, LCPR>, lds);
         k_coef_pred_mfma<B, NK, LCPR><<<grid, kBlock, lds, s>>>(a);
         return;
+    }
+    if constexpr (B <= 2) {
+        if (scores_only(a)) {
+            k_score_pred<B, LCPR><<<grid, kBlock, lat_lds, s>>>(a);
+            return;
+        }
     }
     constexpr bool XR = pred_tokens_in_regs(B, NK);
     const size_t lds = (XR ? 0 : (size_t)B * NK * kColsPerLoad * 2) + lat_lds;
@@ -2517,6 +2573,12 @@ template <int B, int NK>
 static hipError_t coef_tern_launch(const CoefArgs &a, hipStream_t s)
 {
     const int grid = (a.d_ff + kPredRows - 1) / kPredRows;
+    if constexpr (B == 1) {
+        if (scores_only(a)) {
+            k_score_tern<NK><<<grid, kBlock, 0, s>>>(a);
+            return hipGetLastError();
+        }
+    }
     constexpr bool XR = pred_tokens_in_regs(B, NK);
     const size_t lds = XR ? 0 : (size_t)B * NK * kColsPerLoad * 2;
     allow_lds(k_coef_tern<B, NK, XR, pred_waves(NK)>, lds);

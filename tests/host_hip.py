@@ -90,3 +90,14 @@ class Host:
                (line.split(" ") for line in self.lib.host_hip_launches().decode().splitlines())]
         self.lib.host_hip_clear_launches()
         return out
+
+    def ffn_topk(self, h, variant, B, k=0.9):
+        p, lib = PTR, self.lib
+        mats = (p["W_gate"], p["W_up"], p["W_down"])
+        if variant == "dual_tern":
+            return lib.countdown_ffn_tern_topk(h, p["x"], B, *mats, p["theta"], k, None, p["y"],
+                                               None)
+        v = {"mono": 0, "dual_ideal": 1, "dual_pred": 2, "cats": 4}[variant]
+        pred = variant == "dual_pred"
+        return lib.countdown_ffn_topk(h, v, p["x"], B, *mats, p["A_t"] if pred else None,
+                                      p["B_t"] if pred else None, k, None, p["y"], None)

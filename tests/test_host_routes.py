@@ -66,3 +66,22 @@ def test_coefficient_kernel(host, variant, d_model, d_ff, B, rank, kind):
             if k.startswith(("k_batch_", "k_coef_"))]
     assert len(coef) == 1
     assert coef[0].startswith("k_batch_" if kind == MFMA else "k_coef_"), coef
+
+
+@pytest.mark.parametrize("variant,d_model,B,rank,kernel", [
+    ("dual_pred", 1024, 1, 8, "k_score_pred<1,0>"), ("dual_pred", 8192, 2, 1024, "k_score_pred<2,7>"),
+    ("dual_tern", 256, 1, 0, "k_score_tern<1>"), ("dual_tern", 8192, 1, 0, "k_score_tern<16>"),
+])
+def test_predictor_scores_alone(host, variant, d_model, B, rank, kernel):
+    """A threshold of +inf, and the first pass of per-token thresholds, gather nothing."""
+    def coef(launches):
+        return [k for k, _ in launches if k.startswith(("k_batch_", "k_coef_", "k_score_"))]
+
+    assert coef(ffn_launches(host, variant, d_model, 1000, B, rank, float("inf"))) == [kernel]
+    assert coef(ffn_launches(host, variant, d_model, 1000, B, rank, 3e38))[0].startswith("k_coef_")
+    st, h = host.plan(d_model, 1000, B, rank)
+    assert st == host.cd.CD_OK
+    host.launches()
+    assert host.ffn_topk(h, variant, B) == host.cd.CD_OK
+    assert coef(host.launches()) == [kernel]
+    host.lib.countdown_plan_destroy(h)
