@@ -269,13 +269,17 @@ __global__ __launch_bounds__(kBlock) void k_calib_score(const float *__restrict_
     // per tile and thread: two 16-byte chunks of the latent, one of B_t
     const int ra = threadIdx.x / 8, ca = threadIdx.x % 8 * 4;   // rows ra and ra + 32
     const int rb = threadIdx.x / 4, cb = threadIdx.x % 4 * 8;
-    for (int k0 = 0; k0 < R; k0 += kScoreCols) {
-        u32x4 va[2];
+    u32x4 va[2], vb;
+    const auto load = [&](int k0) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             va[h] = *or_zero(m0 + ra + 32 * h < T && k0 + ca < R,
                              reinterpret_cast<const u32x4 *>(lat + (size_t)(m0 + ra + 32 * h) * R + k0 + ca));
-        const u32x4 vb = load16(or_zero(n0 + rb < N && k0 + cb < R, Bt + (size_t)(n0 + rb) * R + k0 + cb));
+        vb = load16(or_zero(n0 + rb < N && k0 + cb < R, Bt + (size_t)(n0 + rb) * R + k0 + cb));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(0);
+    for (int k0 = 0; k0 < R; k0 += kScoreCols) {
         __syncthreads();
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -284,6 +288,7 @@ __global__ __launch_bounds__(kBlock) void k_calib_score(const float *__restrict_
         *reinterpret_cast<float4 *>(db) = make_float4(bf16_lo(vb.x), bf16_hi(vb.x), bf16_lo(vb.y), bf16_hi(vb.y));
         *reinterpret_cast<float4 *>(db + 4) = make_float4(bf16_lo(vb.z), bf16_hi(vb.z), bf16_lo(vb.w), bf16_hi(vb.w));
         __syncthreads();
+        load(k0 + kScoreCols);  // under this tile's products (past R: zeros)
 #pragma unroll
         for (int kk = 0; kk < kScoreCols; kk += 4) {
             const int r16 = lane % kTile, k = kk + lane / kTile;
