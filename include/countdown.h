@@ -263,10 +263,11 @@ cd_status countdown_ffn_residual(cd_plan *plan, int variant, const float *h_in,
  * h = k (d_ff - 1), q = v[floor h] + (h - floor h)(v[floor h + 1] - v[floor h]).
  * Quantiles and the mean are formed in fp64; *thld_out (a DEVICE float) gets
  * the mean rounded to fp32. q_out (DEVICE double[T], may be NULL) gets the
- * per-token quantiles. k in [0, 1]. More than max_batch tokens go through a
- * matrix product over up to 256 tokens at a time, whose fp32 sums may differ
- * from the FFN calls' coefficients in the last bits; up to max_batch tokens the
- * coefficients are those of the FFN calls. Allocates device memory on the first
+ * per-token quantiles. k in [0, 1]. More than max_batch tokens (at
+ * some sizes, more than twice as many) go through a matrix product over up to
+ * 256 tokens at a time, whose fp32 sums may differ from the FFN calls'
+ * coefficients in the last bits; up to max_batch tokens the coefficients are
+ * those of the FFN calls. Allocates device memory on the first
  * call, which stays with the plan (up to 128 MiB; what a call needs beyond that
  * is freed before it returns), and synchronises `stream` before returning.
  */

@@ -584,14 +584,14 @@ struct CalibLayout {
     size_t scratch, coef, bytes;  // byte offsets (the quantiles come first) and the total
 };
 
-CalibLayout calib_layout(const cd_plan *p, int variant, int tc, int T)
+CalibLayout calib_layout(const cd_plan *p, int variant, int tc, int T, bool decode)
 {
     const auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
     CalibLayout l;
     l.scratch = up((size_t)T * sizeof(double));
-    const size_t y = T <= p->max_batch ? (size_t)T * p->d_model : 0;  // the decode kernels' y
-    const size_t f = cdk::calib_scratch_floats(variant, tc, p->d_model, p->d_rank);
-    l.coef = l.scratch + up((f > y ? f : y) * sizeof(float));
+    const size_t f = decode ? (size_t)tc * p->d_model  // the decode kernels' y
+                            : cdk::calib_scratch_floats(variant, tc, p->d_model, p->d_rank);
+    l.coef = l.scratch + up(f * sizeof(float));
     l.bytes = l.coef + (size_t)tc * p->d_ff * sizeof(float);
     return l;
 }
@@ -617,6 +617,32 @@ cd_status calib_reserve(cd_plan *p, size_t bytes)
         p->cal_bytes = bytes;
     }
     return st;
+}
+
+// Whether T calibration tokens go through the FFN's own coefficient kernels, a decode-sized
+// batch at a time, rather than through a matrix product (times of a call, batches against the
+// product). One batch does: it reads the weights once too (1 token of a 4096 x 11008 layer: 38
+// against 58 us). Two do
+//  - with a predictor of rank 512 and more up to 4 tokens, whose scores are a chain of column
+//    tiles in few workgroups (rank 1024, 2 tokens of 4096 x 3000: 47 against 70; 9 tokens of
+//    4096 x 11008 96 against 80);
+//  - past 4096 columns, where the product itself is such a chain: up to 2048 neurons (5 tokens
+//    of 8192 x 688 through a 4-token plan: 37 against 47; 3000 neurons 52 against 49), and the
+//    ternary predictor, which decodes its weights on the way (8192 x 28672: 86 against 148),
+//    but for middle sizes (6000 x 11008, 4 tokens through a 2-token plan: 62 against 57).
+bool calib_decode(const cd_plan *p, int variant, int T)
+{
+    if (T <= p->max_batch)
+        return true;
+    if (T > 2 * p->max_batch)
+        return false;
+    if (variant == CD_VARIANT_DUAL_PRED)
+        return p->d_rank >= 512 && T <= 4;
+    if (p->d_model <= 4096)
+        return false;
+    if (variant == CD_VARIANT_DUAL_TERN)
+        return p->d_model > 6144 || p->d_ff <= 4096 || p->d_ff > 16384;
+    return p->d_ff <= 2048;
 }
 
 cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uint16_t *W_gate,
@@ -650,15 +676,18 @@ cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uin
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // Tokens go through in chunks whose coefficients stay within kCalibCoefBytes;
     // smaller chunks when that does not fit in memory.
+    const bool decode = calib_decode(p, variant, T);
     CalibLayout l;
     const size_t fit = kCalibCoefBytes / ((size_t)p->d_ff * sizeof(float));
     int tc = T < kCalibTokens ? T : kCalibTokens;
     if (fit < (size_t)tc)
         tc = fit > (size_t)p->max_batch ? (int)fit : p->max_batch;
+    if (decode && tc > p->max_batch)
+        tc = p->max_batch;
     for (;; tc /= 2) {
-        l = calib_layout(p, variant, tc, T);
+        l = calib_layout(p, variant, tc, T, decode);
         st = calib_reserve(p, l.bytes);
-        if (st != CD_ENOMEM || tc == 1 || T <= p->max_batch)
+        if (st != CD_ENOMEM || tc == 1)
             break;
     }
     if (st != CD_OK)
@@ -676,29 +705,25 @@ cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uin
     a.Tp = Tp;
     a.scratch = reinterpret_cast<float *>(ws + l.scratch);
     a.coef = reinterpret_cast<float *>(ws + l.coef);
-    if (T <= p->max_batch) {
-        // one decode-sized batch: the FFN's own coefficient kernel reads the weights
-        // once too, and is 5-20 us faster than a matrix-product tile of 32 tokens
-        // (1 token of a 4096 x 11008 layer: 38 against 58 us a call)
-        if (pred)
-            st = launched(cdk::launch_latent(X, T, A_t, p->d_model, p->d_rank, p->lat, s));
-        cdk::CoefArgs c = coef_args(p, X, T, W_gate ? W_gate : W_up, W_up ? W_up : W_gate, B_t,
-                                    INFINITY, a.scratch, Tp);  // y: zeroed, not read
-        c.coef = a.coef;
-        if (st == CD_OK)
-            st = launched(cdk::launch_coef(variant, c, false, s));
-        if (st == CD_OK)
-            st = launched(cdk::launch_select(a.coef, p->d_ff, p->d_ff, T, pred || tern ? 0 : 1, k,
-                                             q, s));
-    } else {
-        for (int t0 = 0; st == CD_OK && t0 < T; t0 += tc) {
-            a.T = T - t0 < tc ? T - t0 : tc;
-            a.X = X + (size_t)t0 * p->d_model;
-            st = launched(cdk::launch_calib_coef(variant, a, s));
+    for (int t0 = 0; st == CD_OK && t0 < T; t0 += tc) {
+        const int n = T - t0 < tc ? T - t0 : tc;
+        const uint16_t *x = X + (size_t)t0 * p->d_model;
+        if (decode) {
+            if (pred)
+                st = launched(cdk::launch_latent(x, n, A_t, p->d_model, p->d_rank, p->lat, s));
+            cdk::CoefArgs c = coef_args(p, x, n, W_gate ? W_gate : W_up, W_up ? W_up : W_gate, B_t,
+                                        INFINITY, a.scratch, Tp);  // y: zeroed, not read
+            c.coef = a.coef;
             if (st == CD_OK)
-                st = launched(cdk::launch_select(a.coef, p->d_ff, p->d_ff, a.T, pred || tern ? 0 : 1,
-                                                 k, q + t0, s));
+                st = launched(cdk::launch_coef(variant, c, false, s));
+        } else {
+            a.T = n;
+            a.X = x;
+            st = launched(cdk::launch_calib_coef(variant, a, s));
         }
+        if (st == CD_OK)
+            st = launched(cdk::launch_select(a.coef, p->d_ff, p->d_ff, n, pred || tern ? 0 : 1, k,
+                                             q + t0, s));
     }
     // a calibration is not an FFN call: down-only calls and exports need one first
     forget_state(p);

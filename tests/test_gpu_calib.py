@@ -36,6 +36,10 @@ CASES = [
     ("dual_pred", 300, 1544, 264, 256), ("dual_pred", 33, 136, 72, 1024),
     ("dual_tern", 31, 256, 136, 0), ("dual_tern", 70, 1544, 200, 0),
     ("dual_tern", 33, 8192, 64, 0),
+    # two batches of the plan's one token past 4096 columns: the decode kernels; three: the product
+    ("mono", 2, 4104, 40, 0), ("dual_ideal", 2, 8192, 40, 0), ("dual_tern", 2, 4104, 72, 0),
+    ("cats", 3, 4104, 40, 0), ("dual_tern", 3, 8192, 72, 0), ("mono", 2, 4104, 2056, 0),
+    ("dual_pred", 2, 264, 72, 512), ("dual_pred", 3, 136, 72, 1024),
 ]
 
 

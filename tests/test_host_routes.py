@@ -85,3 +85,27 @@ def test_predictor_scores_alone(host, variant, d_model, B, rank, kernel):
     assert host.ffn_topk(h, variant, B) == host.cd.CD_OK
     assert coef(host.launches()) == [kernel]
     host.lib.countdown_plan_destroy(h)
+
+
+@pytest.mark.parametrize("variant,d_model,d_ff,mb,T,rank,batches", [
+    ("mono", 4096, 11008, 1, 1, 0, 1), ("dual_pred", 256, 688, 8, 8, 64, 1),
+    ("mono", 4096, 688, 1, 2, 0, 0), ("cats", 4104, 2048, 4, 8, 0, 2), ("mono", 8192, 688, 4, 5, 0, 2),
+    ("mono", 8192, 2056, 1, 2, 0, 0), ("mono", 8192, 688, 4, 9, 0, 0),
+    ("dual_tern", 4104, 28672, 2, 4, 0, 2), ("dual_tern", 8192, 688, 1, 3, 0, 0),
+    ("dual_tern", 6144, 11008, 2, 4, 0, 0), ("dual_tern", 6152, 11008, 2, 4, 0, 2),
+    ("dual_tern", 6144, 4096, 1, 2, 0, 2), ("dual_tern", 6144, 16392, 1, 2, 0, 2),
+    ("dual_pred", 8192, 688, 1, 2, 256, 0), ("dual_pred", 256, 688, 1, 2, 512, 2),
+    ("dual_pred", 256, 688, 2, 4, 1024, 2), ("dual_pred", 256, 688, 4, 5, 1024, 0),
+])
+def test_calibration_route(host, variant, d_model, d_ff, mb, T, rank, batches):
+    """Decode-sized batches (their number), or 0: one matrix product."""
+    st, h = host.plan(d_model, d_ff, mb, rank)
+    assert st == host.cd.CD_OK
+    host.launches()
+    assert host.calibrate(h, variant, T) == host.cd.CD_OK
+    names = [k for k, _ in host.launches()]
+    decode = [k for k in names if k.startswith(("k_batch_", "k_coef_", "k_score_"))]
+    assert len(decode) == batches
+    assert any(k.startswith("k_calib_") for k in names) == (batches == 0)
+    assert sum(k.startswith("k_topk_select") for k in names) == max(batches, 1)
+    host.lib.countdown_plan_destroy(h)
