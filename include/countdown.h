@@ -248,6 +248,8 @@ cd_status countdown_ternary_pack(const int8_t *theta_t, int d_model, int d_ff, u
  * thld is ignored for CD_VARIANT_DENSE; A_t / B_t as for countdown_ffn_dual
  * (both set exactly for CD_VARIANT_DUAL_PRED, else NULL). With the predictor
  * the normalisation is computed inside the latent product's kernel.
+ * At 3-8 tokens the coefficients may differ in the last bits from those of
+ * the plain call on the same x (another order of the fp32 sums).
  */
 cd_status countdown_ffn_residual(cd_plan *plan, int variant, const float *h_in,
                                  const float *y_prev, float *h_out, float eps, uint16_t *x_out,

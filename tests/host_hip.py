@@ -101,3 +101,12 @@ class Host:
         pred = variant == "dual_pred"
         return lib.countdown_ffn_topk(h, v, p["x"], B, *mats, p["A_t"] if pred else None,
                                       p["B_t"] if pred else None, k, None, p["y"], None)
+
+    def residual(self, h, variant, B, thld=1.0):
+        p = PTR
+        v = {"mono": 0, "dual_ideal": 1, "dual_pred": 2, "dense": 3, "cats": 4}[variant]
+        pred = variant == "dual_pred"
+        return self.lib.countdown_ffn_residual(
+            h, v, p["h_in"], None, p["h_out"], 1e-5, p["x"], B, p["W_gate"], p["W_up"],
+            p["W_down"], p["A_t"] if pred else None, p["B_t"] if pred else None, thld, p["y"],
+            None)

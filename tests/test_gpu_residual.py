@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 EPS = 1e-5
 X_SLACK = 1e-5  # relative: fp32 sum of squares and scaling against the fp64 oracle
 
-VID = {"mono": 0, "dual_ideal": 1, "dual_pred": 2, "dense": 3}
+VID = {"mono": 0, "dual_ideal": 1, "dual_pred": 2, "dense": 3, "cats": 4}
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -89,6 +89,46 @@ def test_residual_layer(variant, shape):
     h_gpu, x_bits, out = run_residual(plan, variant, layer, h_in, y_prev, thld)
     check_norm(h_in, y_prev, h_gpu, x_bits, label)
     check_call(variant, layer, x_bits, thld, out, label)
+
+
+# The kernels that only residual layers run past 2 tokens: the token tiles of 4 and 8 (full and
+# partly empty), every chunk count of columns (one, two, four, eight; sixteen at 4 tokens), every
+# rank (the latent in LDS and the narrow weight tiles at 1024), CATS.
+BATCHES = [
+    ("cats", 264, 520, 3, 0), ("cats", 1032, 264, 8, 0), ("cats", 4096, 200, 5, 0),
+    ("cats", 8192, 136, 4, 0), ("mono", 264, 520, 5, 0), ("mono", 520, 136, 8, 0),
+    ("mono", 4096, 264, 8, 0), ("mono", 4096, 264, 4, 0), ("mono", 8192, 104, 3, 0),
+    ("dual_ideal", 264, 520, 8, 0), ("dual_ideal", 520, 136, 4, 0), ("dual_ideal", 4096, 136, 7, 0),
+    ("dual_ideal", 8192, 104, 4, 0), ("dense", 264, 136, 4, 0), ("dense", 4096, 136, 8, 0),
+    ("dense", 8192, 104, 3, 0),
+    ("dual_pred", 264, 520, 3, 8), ("dual_pred", 264, 520, 8, 16), ("dual_pred", 1032, 264, 5, 32),
+    ("dual_pred", 520, 264, 6, 64), ("dual_pred", 2048, 264, 4, 128), ("dual_pred", 4096, 264, 8, 256),
+    ("dual_pred", 4096, 264, 3, 512), ("dual_pred", 1032, 264, 8, 512), ("dual_pred", 264, 264, 4, 1024),
+    ("dual_pred", 520, 264, 8, 1024), ("dual_pred", 2056, 136, 8, 1024), ("dual_pred", 4096, 136, 5, 1024),
+    ("dual_pred", 8192, 136, 3, 8), ("dual_pred", 8192, 136, 4, 1024),
+]
+
+
+@pytest.mark.parametrize("variant,dm,dff,B,rank", BATCHES)
+def test_residual_layer_batches(variant, dm, dff, B, rank):
+    from workloads.synth import bf16_round
+
+    L = make_layer(960 + rank, dm, dff, 0.03)
+    P = make_predictor(960 + rank, dm, rank, dff, 0.05) if rank else None
+    layer = Layer(L, P)
+    h_in, y_prev = residual_inputs(dm + B + rank, B, dm)
+    X = np.stack([oracle.residual_rmsnorm(h_in[b], y_prev[b], eps=EPS)[1] for b in range(B)])
+    X = bf16_round(np.array(X, dtype=np.float32))
+    plan = plan_for(layer, max_batch=B)
+    for k in (0.8, 0.3):  # few active neurons (of a batch) and most
+        thld = 0.0 if variant == "dense" else float(np.float32(oracle.calibrate(
+            variant, X, k, W_gate=L["W_gate"], W_up=L["W_up"], A_t=None if P is None else P["A_t"],
+            B_t=None if P is None else P["B_t"])[0]))
+        label = f"residual {variant} {dm}x{dff} B{B} rank {rank} k {k}"
+        h_gpu, x_bits, out = run_residual(plan, variant, layer, h_in, y_prev, thld)
+        check_norm(h_in, y_prev, h_gpu, x_bits, label)
+        check_call(variant, layer, x_bits, thld, out, label)
+    plan.close()
 
 
 def test_residual_rejects_overlap():

@@ -109,3 +109,17 @@ def test_calibration_route(host, variant, d_model, d_ff, mb, T, rank, batches):
     assert any(k.startswith("k_calib_") for k in names) == (batches == 0)
     assert sum(k.startswith("k_topk_select") for k in names) == max(batches, 1)
     host.lib.countdown_plan_destroy(h)
+
+
+@pytest.mark.parametrize("variant,B,rank,kernel", [
+    ("mono", 4, 0, "k_coef_mono<4,8,false,false>"), ("cats", 8, 0, "k_coef_mono<8,8,false,true>"),
+    ("dual_ideal", 3, 0, "k_coef_dual<4,8,false,false>"), ("dual_pred", 4, 256, "k_coef_pred<4,8,false,5,8>"),
+    ("dual_pred", 8, 256, "k_coef_pred_mfma<8,8,5>"), ("dense", 8, 0, "k_batch_dual<2,4>"),
+])
+def test_residual_layers_keep_the_order_of_their_sums(host, variant, B, rank, kernel):
+    st, h = host.plan(4096, 14336, B, rank)
+    assert st == host.cd.CD_OK
+    host.launches()
+    assert host.residual(h, variant, B) == host.cd.CD_OK
+    assert [k for k, _ in host.launches() if k.startswith(("k_coef_", "k_batch_"))] == [kernel]
+    host.lib.countdown_plan_destroy(h)
