@@ -1,4 +1,4 @@
-// Coefficient and gather kernels for batches of 3-8 tokens. Part of
+// Coefficient and gather kernels for batches of 3-8 tokens (where: batch_coef). Part of
 // cd_kernels.hip (its only includer).
 //
 // At 3-8 tokens a row's products with the batch are a thin matrix product. These
@@ -10,12 +10,12 @@
 //     the matrix core after one exchange between neighbouring lanes, with no staging
 //     of weights through LDS;
 //   - the eight waves of a workgroup take an eighth of the columns each, and keep
-//     their slice of the tokens in registers (16 to 32 of them): there is no token
+//     their slice of the tokens in registers (4 to 32 of them): there is no token
 //     copy in LDS (32-64 KB, reloaded by every four or 32 neurons before, and read
 //     once per token and weight chunk), and a weight chunk costs 2 MFMA
 //     instructions per four tokens instead of 4 v_dot2 per token.
-// A workgroup owns kPredRows = 32 neurons, eight row quads; a wave keeps about 16
-// loads (16 KB) in flight over the next quads. The waves' sums of a quad meet in
+// A workgroup owns up to kPredRows = 32 neurons, eight row quads; a wave keeps up to
+// eight loads (8 KB) in flight over the next quads. The waves' sums of a quad meet in
 // LDS, and from there one thread per (token, neuron) goes on: threshold, union,
 // compaction of the active neurons to dense quads for the gather of the second
 // projection(s), s.
@@ -203,7 +203,8 @@ struct PartSums {
 // matrices a quad is two items, one per matrix, in turn. Up to 8 loads (8 KB) are in
 // flight per wave: with 16 the two workgroups of a CU hold 256 KB in flight, and every
 // case measured the same or slower (dense 4096 x 14336 at 8 tokens 72.8 against 65.1 us,
-// where 128 registers spilled; M at 4 tokens 40.7 against 39.7). row(q, i): the row within the block at position i of quad q, < 0 for none.
+// where 128 registers spilled; M at 4 tokens 40.7 against 39.7). row(q, i): the row
+// within the block at position i of quad q, < 0 for none.
 // Loads past the last quad read nothing (an outside offset), so the loop has no
 // branches around loads. SORT: the tokens are still as loaded; they are sorted behind
 // the first weight loads.

@@ -15,10 +15,11 @@
 // buffers, one barrier per tile, and DEPTH tiles in flight in registers. What
 // bounds it is LDS traffic and the vector instructions of the sums: a single
 // MFMA chain over 4096 columns rounds more often than the decode kernels' sums
-// (relative error of the quantiles 7.5e-8 against 4.9e-8 there), so every 128
-// columns, 64 up to kFineCols, the accumulators go into a compensated fp32 sum
-// (fold(): 3.8e-8 at 4096 columns, 3.9e-8 at 256 where the decode kernels have
-// 4.2e-8). At 256 tokens of 4096 x 11008 the whole call takes 90 us.
+// (relative error of the quantiles against fp64 7.5e-8; theirs 4.7e-8), so every
+// 128 columns, 64 up to kFineCols, the accumulators go into a compensated fp32 sum
+// (fold(): 3.8e-8 at 4096 columns, 3.1e-8 at 2048 and 3.5e-8 at 256, the decode
+// kernels 4.7e-8, 5.1e-8 and 3.7e-8; means over 8 layers of 256 tokens). At 256
+// tokens of 4096 x 11008 the whole call takes 78 us.
 #pragma once
 
 #include "cd_device.hpp"
@@ -342,9 +343,12 @@ hipError_t gemm(const GemmArgs &a, int splits, hipStream_t s)
 {
     // Up to 32 tokens the product is a stream of W: small tiles, 256 bytes of a row
     // at a time (8192 x 28672 at 32 tokens: 149 us a call, 789 as 8 decode batches).
-    // Past that 64 x 64, three workgroups to a CU: 57 us at 256 tokens of 4096 x
-    // 11008 (400 TFLOP/s), against 67 for 128 x 64 tiles, whose 344 workgroups leave
-    // two thirds of the CUs half loaded.
+    // Past that 64 x 64, three workgroups to a CU: a call of 256 tokens of 4096 x 11008
+    // takes 78 us, with 128 x 64 tiles, whose 344 workgroups leave two thirds of the CUs
+    // half loaded, 91; 64 tokens there 54 against 72. With many more workgroups 64 x 64
+    // stays ahead too (256 tokens of 8192 x 28672: 272 against 291 us), but for 128 tokens
+    // of 14336 neurons and more at 4096 columns and up (98 against 96; 8192 x 28672: 193
+    // against 172).
     if (a.T <= 32)
         return gemm_launch<32, 32, 128, 2, KIND>(a, splits, s);
     return gemm_launch<64, KIND == kGemmPair ? 32 : 64, 64, 2, KIND>(a, splits, s);

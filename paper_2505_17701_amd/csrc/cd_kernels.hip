@@ -10,9 +10,10 @@
 //     v_dot2_f32_bf16, reduces across the wave with DPP and applies the
 //     strict threshold (union over the batch). Batches of 3-8 run the MFMA
 //     kernels of cd_batch.hpp instead, but for small layers (batch_coef) and
-//     residual stacks (launch_coef). For M-CountDown an active neuron's wave immediately reads its W_gate row and forms s = u *
-//     SiLU(g). Results land in per-neuron arrays act[d_ff] and s[B][d_ff];
-//     there are no barriers between waves. The kernel also zeroes y.
+//     residual stacks (launch_coef). For M-CountDown an active neuron's wave
+//     immediately reads its W_gate row and forms s = u * SiLU(g). Results land
+//     in per-neuron arrays act[d_ff] and s[B][d_ff]; there are no barriers
+//     between waves. The kernel also zeroes y.
 //   predictor (practical D-CountDown): the latent x . theta_A (one workgroup
 //     per A_t row), then a coefficient kernel over blocks of 32 neurons: B_t
 //     scores, signed threshold, and the block's active neurons dealt to its
@@ -22,7 +23,7 @@
 //     neuron range g. One round trip reads act and s of the range, a wave
 //     ballot compacts the active neurons in ascending order into LDS; for 1-2
 //     tokens each wave then keeps 16 W_down rows in flight on the VALU, for
-//     4-8 the rows feed MFMA (S as bf16 hi + lo); partial sums are added in
+//     3-8 the rows feed MFMA (S as bf16 hi + lo); partial sums are added in
 //     LDS and go to y with one fp32 atomic per column and token.
 //   per-token threshold: the coefficient kernel writes the dense
 //     coefficients, one workgroup per token selects its quantile (one wide
@@ -481,7 +482,7 @@ __device__ __forceinline__ void pred_finish(const CoefArgs &a, const Tokens<B, N
     }
 }
 
-// Next neuron of this wave's share of the block mask (every fourth active
+// Next neuron of this wave's share of the block mask (every NW-th active
 // neuron), or -1; advances the mask past it.
 template <int NW>
 __device__ __forceinline__ int pred_next(uint32_t &m)
@@ -495,9 +496,8 @@ __device__ __forceinline__ int pred_next(uint32_t &m)
     return r;
 }
 
-// This wave's share of the block's active neurons: the waves' masks are
-// joined (one barrier) and every fourth active neuron, starting at number
-// `wave`, is kept.
+// The block's active neurons from number `wave` on, of which the wave takes every
+// NW-th (pred_next): the scoring waves' masks, joined (one barrier).
 __device__ __forceinline__ uint32_t block_share(uint32_t *wflag, uint32_t wmask, int wave, int lane)
 {
     if (lane == 0 && wave < kWavesPerBlock)  // the scoring waves
@@ -649,12 +649,10 @@ struct WtShape {
     static constexpr int kLoads = kTile / kRowsPerLoad;   // loads per lane and matrix
 };
 
-// batch widths: the low-rank kernel's 256 columns with one batch in flight
-// per wave measured 1-1.5% faster at 5-8 tokens than 128 columns with two in
-// flight (two 256-column batches take 254 VGPRs, one wave per SIMD); the
-// ternary kernel, and the low-rank one at rank 1024 (latent in LDS), keep
-// 128-column batches, two in flight (with 256 columns the ternary layer took
-// 80.7 against 64.4 us at 8 tokens)
+// batch widths: 256 columns with one batch in flight per wave measured 1-1.5%
+// faster at 5-8 tokens than 128 columns with two in flight (two 256-column
+// batches take 254 VGPRs, one wave per SIMD); at rank 1024 (latent in LDS)
+// 128-column batches, two in flight
 constexpr int kWtStepsWide = 8;
 constexpr int kWtStepsNarrow = 4;
 
@@ -728,13 +726,11 @@ __device__ __forceinline__ void wt_consume(uint16_t *wt, const WtBatch<STEPS> &b
 // each tile's column steps are split among 4 / ntiles waves, which add their
 // 16 x 16 partial sums in `part` (LDS [4][2][256] fp32) and write s = u * SiLU(g).
 // wtiles: LDS [4 waves][WtShape<STEPS>::kWaveElems] bf16; lrow: LDS [32] rows
-// of the active neurons. INTERLEAVE: wave kw of a tile takes batches kw,
-// kw + wpt, ... of STEPS steps, so the tile's waves read adjacent pieces of
-// each row together (after the low-rank score: 57.5 -> 56.7 us per 8B layer at
-// 8 tokens); otherwise each takes one contiguous run of steps (the ternary
-// kernel: interleaved, its layer took 68.2 against 65.4 us). A wave keeps two
-// batches in flight at 4 steps, one at 8.
-template <int B, int NK, bool INTERLEAVE, int STEPS>
+// of the active neurons. Wave kw of a tile takes batches kw, kw + wpt, ... of STEPS
+// steps, so the tile's waves read adjacent pieces of each row together (a
+// contiguous run of steps per wave: 57.5 against 56.7 us per 8B layer at 8 tokens).
+// A wave keeps two batches in flight at 4 steps, one at 8.
+template <int B, int STEPS>
 __device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wtiles, float *part,
                                                 int *lrow, uint32_t M, int r0, int wave, int lane)
 {
@@ -753,7 +749,6 @@ __device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wti
     const int i = lane % kTile, g = lane / kTile;
     const int steps = (a.d_model + 31) / 32;
     const int nbat = (steps + kWtSteps - 1) / kWtSteps;  // batches of kWtSteps steps
-    (void)nbat;
     const bool xreal = i < a.nb;
     const uint16_t *xrow = a.x + (size_t)(xreal ? i : 0) * a.d_model;
     int row[kWtLoads];
@@ -767,12 +762,12 @@ __device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wti
     uint16_t *wt = wtiles + (size_t)wave * W::kWaveElems;
     f32x4_t dg = {0.0f, 0.0f, 0.0f, 0.0f}, du = {0.0f, 0.0f, 0.0f, 0.0f};
     WtBatch<STEPS> b0, b1;  // 4 steps: the next batch is in flight while this one is consumed
-    if constexpr (INTERLEAVE && STEPS >= kWtStepsWide) {
+    if constexpr (STEPS >= kWtStepsWide) {
         for (int j = kw; j < nbat; j += wpt) {
             wt_load(b0, a, row, have, xrow, xreal, j * kWtSteps, steps, lane);
             wt_consume(wt, b0, j * kWtSteps, steps, lane, dg, du);
         }
-    } else if constexpr (INTERLEAVE) {
+    } else {
         if (kw < nbat)
             wt_load(b0, a, row, have, xrow, xreal, kw * kWtSteps, steps, lane);
         for (int j = kw; j < nbat; j += 2 * wpt) {
@@ -785,21 +780,6 @@ __device__ __forceinline__ void gather_mfma_lds(const CoefArgs &a, uint16_t *wti
             if (jb + wpt < nbat)
                 wt_load(b0, a, row, have, xrow, xreal, (jb + wpt) * kWtSteps, steps, lane);
             wt_consume(wt, b1, jb * kWtSteps, steps, lane, dg, du);
-        }
-    } else {
-        const int sw = (steps + wpt - 1) / wpt;  // this wave's steps [s0, s1)
-        const int s0 = min(steps, kw * sw), s1 = min(steps, s0 + sw);
-        wt_load(b0, a, row, have, xrow, xreal, s0, s1, lane);
-        for (int s = s0; s < s1; s += 2 * kWtSteps) {
-            const int sb = s + kWtSteps;
-            if (sb < s1)
-                wt_load(b1, a, row, have, xrow, xreal, sb, s1, lane);
-            wt_consume(wt, b0, s, s1, lane, dg, du);
-            if (sb >= s1)
-                break;
-            if (sb + kWtSteps < s1)
-                wt_load(b0, a, row, have, xrow, xreal, sb + kWtSteps, s1, lane);
-            wt_consume(wt, b1, sb, s1, lane, dg, du);
         }
     }
 #pragma unroll
@@ -865,7 +845,7 @@ __global__ __launch_bounds__(kBlock) void k_coef_pred_mfma(const CoefArgs a)
     for (int v = 0; v < kWavesPerBlock; ++v)
         M |= wflag[v] << (v * kPredRowsPerWave);
     // the latent is no longer read once gather_mfma_lds's first barrier has passed
-    gather_mfma_lds<B, NK, true, STEPS>(a, wtiles, reinterpret_cast<float *>(latw), lrow, M, r0,
+    gather_mfma_lds<B, STEPS>(a, wtiles, reinterpret_cast<float *>(latw), lrow, M, r0,
                                         wave, lane);
 }
 
@@ -1796,7 +1776,7 @@ __global__ __launch_bounds__(kBlock) void k_mean(const double *__restrict__ q, i
 // The per-token form of Eq. 6: each token's threshold is the quantile of its
 // own coefficients. The coefficient kernel first writes the dense
 // coefficients (threshold +inf, nothing gathered); k_topk_select finds each
-// token's quantile; k_gather_topk thresholds against it and gathers.
+// token's quantile; k_gather_topk_w or k_batch_topk thresholds against it and gathers.
 
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkPerThread = 32;  // keys per thread: d_ff <= 32768
