@@ -49,7 +49,15 @@ struct cd_plan {
 
 namespace {
 
-cd_status hip_status(hipError_t e) { return e == hipSuccess ? CD_OK : CD_EHIP; }
+// Status of a HIP call that is no launch. The caller reports the failure; HIP would keep it for
+// the hipGetLastError of the next launch on this thread (later successes do not clear it).
+cd_status hip_status(hipError_t e)
+{
+    if (e == hipSuccess)
+        return CD_OK;
+    (void)hipGetLastError();
+    return CD_EHIP;
+}
 
 cd_status launched(hipError_t e) { return e == hipSuccess ? CD_OK : CD_EHIP; }
 
@@ -116,7 +124,7 @@ bool overlaps(const void *a, size_t na, const void *b, size_t nb)
 cd_status plan_device_ok(const cd_plan *p)
 {
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess)
+    if (hip_status(hipGetDevice(&dev)) != CD_OK)
         return CD_EHIP;
     return dev == p->device ? CD_OK : CD_EINVAL;
 }
@@ -399,10 +407,8 @@ cd_status dalloc(T **ptr, size_t count)
     if (e == hipSuccess)
         return CD_OK;
     *ptr = nullptr;
-    // This call reports the failure; HIP would keep it for the hipGetLastError of the next
-    // launch on this thread (later successes do not clear it).
-    (void)hipGetLastError();
-    return e == hipErrorOutOfMemory ? CD_ENOMEM : CD_EHIP;
+    const cd_status st = hip_status(e);
+    return e == hipErrorOutOfMemory ? CD_ENOMEM : st;
 }
 
 void release(cd_plan *p)
@@ -486,7 +492,7 @@ cd_status countdown_plan_create(int d_model, int d_ff, int max_batch, int d_rank
     if (flags & ~(CD_PLAN_KEEP_COEF | CD_PLAN_DETERMINISTIC))
         return CD_EINVAL;
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess)
+    if (hip_status(hipGetDevice(&dev)) != CD_OK)
         return CD_EHIP;
     cd_plan *p = new (std::nothrow) cd_plan();
     if (!p)
@@ -732,9 +738,9 @@ cd_status calibrate(cd_plan *p, int variant, const uint16_t *X, int T, const uin
         st = hip_status(cdk::launch_mean(q, T, thld_out, q8 ? q_out : nullptr, s));
     if (st == CD_OK && q_out && !q8)
         st = hip_status(hipMemcpyAsync(q_out, q, sizeof(double) * T, hipMemcpyDeviceToDevice, s));
-    const hipError_t se = hipStreamSynchronize(s);
-    if (st == CD_OK && se != hipSuccess)
-        st = CD_EHIP;
+    const cd_status done = hip_status(hipStreamSynchronize(s));
+    if (st == CD_OK)
+        st = done;
     if (p->cal_bytes > kCalibKeepBytes)
         calib_free(p);
     return st;
@@ -879,7 +885,7 @@ void *g_scratch_ptr[kNoallocMaxDevices];  // per device, set once
 cd_status scratch_on_current_device(int *dev_out, void **out)
 {
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess)
+    if (hip_status(hipGetDevice(&dev)) != CD_OK)
         return CD_EHIP;
     if (dev < 0 || dev >= kNoallocMaxDevices)
         return CD_EUNSUPPORTED;
@@ -887,7 +893,7 @@ cd_status scratch_on_current_device(int *dev_out, void **out)
     if (!g_scratch_ptr[dev]) {
         void *p = nullptr;
         const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
+        if (hip_status(e) != CD_OK || !p)
             return CD_EHIP;
         g_scratch_ptr[dev] = p;
     }

@@ -16,6 +16,7 @@ namespace {
 hipError_t last_error = hipSuccess;
 size_t malloc_limit = ~(size_t)0;  // larger requests fail
 long live = 0;                     // allocations not freed yet
+bool sync_fails = false;           // as under stream capture
 std::string launches;
 dim3 cfg_grid, cfg_block;
 size_t cfg_lds;
@@ -35,6 +36,7 @@ std::map<const void *, std::string> &names()
 extern "C" {
 
 void host_hip_set_malloc_limit(size_t bytes) { malloc_limit = bytes; }
+void host_hip_set_sync_fails(int fails) { sync_fails = fails != 0; }
 long host_hip_live_allocations(void) { return live; }
 void host_hip_clear_launches(void) { launches.clear(); }
 // one line per launch: kernel<template arguments> grid.x grid.y block.x dynamic LDS bytes
@@ -71,7 +73,10 @@ hipError_t hipGetDevice(int *d)
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t)
+{
+    return sync_fails ? fail(hipErrorStreamCaptureUnsupported) : hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
 

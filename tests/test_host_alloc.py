@@ -1,7 +1,7 @@
-"""Device memory that runs out: a failed allocation is reported by the call that made it and
-by no other. HIP keeps a failed call's error until hipGetLastError reads it, and every launch
-is checked with hipGetLastError, so an error left behind by a failed allocation would be
-taken for a failed launch."""
+"""Device memory that runs out, a wait that fails: the error is reported by the call that met
+it and by no other. HIP keeps a failed call's error until hipGetLastError reads it, and every launch
+is checked with hipGetLastError, so an error left behind by another call would be taken for
+a failed launch."""
 import pytest
 
 import host_hip
@@ -59,5 +59,19 @@ def test_plan_without_memory_fails_alone(host):
         host.limit()
     assert st == host.cd.CD_ENOMEM
     assert host.lib.host_hip_live_allocations() == before
+    assert host.ffn(h, "mono", 1) == host.cd.CD_OK
+    host.lib.countdown_plan_destroy(h)
+
+
+def test_calibration_under_capture_fails_alone(host):
+    """A calibration waits for its stream, which a capture refuses: CD_EHIP, and the next
+    call's launches are not taken for failed ones."""
+    st, h = host.plan(256, 688)
+    assert st == host.cd.CD_OK
+    host.lib.host_hip_set_sync_fails(1)
+    try:
+        assert host.calibrate(h, "mono", 40) == host.cd.CD_EHIP
+    finally:
+        host.lib.host_hip_set_sync_fails(0)
     assert host.ffn(h, "mono", 1) == host.cd.CD_OK
     host.lib.countdown_plan_destroy(h)
