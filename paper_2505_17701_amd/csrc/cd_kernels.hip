@@ -2634,7 +2634,7 @@ static hipError_t coef_b(int variant, const CoefArgs &a, hipStream_t s)
 // the order of a coefficient's sums: x is rounded to bf16 between the layers, a last-bit
 // difference moves it by a step, and that moves neurons across later thresholds (one more or
 // less moves y by 1-4%). Measured on 180 stacks of 3 layers at 3-8 tokens, 1000-4096 columns,
-// against the builds before the MFMA kernels: with these kernels a deterministic plan's y is
+// against results from before the MFMA kernels: with these kernels a deterministic plan's y is
 // the same bits in all, and the default plan's (fp32 atomics) differs as much as two of its
 // own runs do (median 4e-5, 3% of the stacks more than 2e-2); with the MFMA kernels y differs
 // by a median of 5e-4, and in 17% of the stacks by more than 2e-2, up to 0.11. Each layer by
